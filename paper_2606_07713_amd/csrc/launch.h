@@ -64,8 +64,11 @@ hipError_t launch_prefill_gather(const Problem& p, const GatherLayout& g, hipStr
 hipError_t launch_prefill_bf16(const Problem& p, hipStream_t stream);
 
 
-// Prefill, fp32 inputs: one launch of the fp32 vector-ALU tile kernel.
+// Prefill, fp32 inputs: one launch of the fp32 vector-ALU kernel (smallest
+// grids) or of the fp32 matrix-core kernel.
 hipError_t launch_prefill_f32(const Problem& p, hipStream_t stream);
+// The matrix-core kernel alone; `cus` = compute units of the device.
+hipError_t launch_prefill_f32_mfma(const Problem& p, int cus, hipStream_t stream);
 
 // Decode (Nq == 1): split-K partial kernel + combine kernel.
 // `ws` holds bh*splits*(d + 2) floats.

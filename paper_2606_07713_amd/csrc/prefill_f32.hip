@@ -1,10 +1,11 @@
-// Fused attention prefill for fp32 inputs and fp32 output (vector ALU, fp32
-// throughout).
+// Fused attention prefill for fp32 inputs and fp32 output: the vector-ALU
+// kernel of the smallest grids, and the choice between it and the fp32
+// matrix-core kernel (prefill_f32_mfma.hip).
 //
-// Used where the inputs are fp32 and the result must stay within fp32
-// rounding of the exact attention (no bf16 rounding of any operand).  One
-// workgroup owns a tile of query rows of one (batch*head); each row is
-// handled by QL lanes that split d (4, 8 or 16).  The waves of a workgroup hold
+// The result must stay within fp32 rounding of the exact attention (no bf16
+// rounding of any operand).  One workgroup owns a tile of query rows of one
+// (batch*head); each row is handled by QL lanes that split d (8 or 16).  The
+// waves of a workgroup hold
 // the same rows and walk disjoint key streams (wave w takes tiles w,
 // w + STREAMS, ...; 128 keys per round of the workgroup), each staging its
 // own K/V tiles in its own LDS area, read by its lanes as broadcasts.  At the
@@ -189,27 +190,6 @@ __global__ __launch_bounds__(threads_of<STREAMS>()) void prefill_f32_kernel(
     }
 }
 
-// Four shapes of workgroup, by grid size (raw C-ABI calls, us, one box):
-//
-//   streams x key tile, lanes per row, rows   8x16,4,16  16x8,4,16  16x8,8,8  16x8,16,4
-//   B1 H1 128 x 128, d = 64                    6.39       6.83       4.97      4.57
-//   B1 H1 128 x 128, d = 128                   9.73       10.27      6.73      5.40
-//   B1 H2 300 x 517, d = 128                   31.7       27.9       17.1      13.3
-//   B1 H1 1K x 1K causal, d = 64               -          -          17.2      14.5
-//   B1 H1 2K x 2K causal, d = 128              103.1      88.9       56.5      56.4
-//   B1 H1 4K x 4K, d = 64                      128.8      121.4      146.6     -
-//   B4 H8 256 x 256, d = 64                    16.5       17.7       22.4      -
-//   B1 H16 1K x 1K, d = 64                     100.9      101.2      140.7     -
-//
-// Splitting a row over more lanes shortens each wave's chain and multiplies
-// the grid; it pays while the grid still fits the GPU.  So: 16 lanes per row
-// (4 rows per workgroup) while that grid fits the compute units, else 8 lanes
-// (8 rows) while that one does, all with sixteen key streams; long keys on
-// grids of up to one 16-row workgroup per unit take sixteen streams of 16
-// rows; everything else eight streams of 16 rows, whose workgroups are the
-// cheapest to start and merge.
-constexpr int kWideMinKeys = 512;
-
 template <int D, bool CAUSAL, int STREAMS, int QL>
 hipError_t launch_s(const Problem& p, hipStream_t stream) {
     constexpr int ROWS = rows_of<QL>();
@@ -222,16 +202,34 @@ hipError_t launch_s(const Problem& p, hipStream_t stream) {
                          p.scale * kLog2e, p.lay);
 }
 
+// Which kernel.  Splitting a row over many lanes shortens each wave's chain
+// and multiplies the grid: 16 lanes per row (4 rows per workgroup) are the
+// fastest while that grid fits the compute units, 8 lanes (8 rows) on the next
+// larger grids at d = 128 while the keys are few; everything else belongs to
+// the matrix-core kernel.  us, raw calls, one box:
+//
+//                                       16 lanes  8 lanes  matrix cores
+//   B1 H1 128 x 128, d = 64               4.5       5.0       4.5
+//   B2 H8 17 x 600 causal, d = 64         9.7       -         10.8
+//   B1 H1 1K x 1K, d = 64                 16.4      17.2      14.6
+//   B1 H4 100 x 4096, d = 64              50.6      -         45.7
+//   B1 H1 128 x 128, d = 128              5.4       6.7       6.9
+//   B1 H2 300 x 517, d = 128              13.4      17.1      15.7
+//   B1 H1 1K x 1K causal, d = 128         22.8      -         25.1
+//   B1 H16 128 x 128 causal, d = 128      -         7.0       7.3
+//   B1 H20 128 x 128, d = 64              -         -         4.6 (8 streams of 16 rows: 6.7)
+//   B1 H8 256 x 256, d = 128              -         11.1      9.8
+//   B1 H1 2K x 2K causal, d = 128         56.2      56.5      43.4
 template <int D, bool CAUSAL>
 hipError_t launch(const Problem& p, hipStream_t stream) {
     const long long blocks16 = (long long)p.bh * ((p.nq + 15) / 16);
     int cus = 0;
     const hipError_t e = pf::device_cus(stream, cus);
     if (e != hipSuccess) return e;
-    if (4 * blocks16 <= cus) return launch_s<D, CAUSAL, 16, 16>(p, stream);
-    if (2 * blocks16 <= cus) return launch_s<D, CAUSAL, 16, 8>(p, stream);
-    if (p.nk >= kWideMinKeys && blocks16 <= cus) return launch_s<D, CAUSAL, 16, 4>(p, stream);
-    return launch_s<D, CAUSAL, 8, 4>(p, stream);
+    if (4 * blocks16 <= cus && (D == 128 || p.nk < 1000)) return launch_s<D, CAUSAL, 16, 16>(p, stream);
+    if constexpr (D == 128)
+        if (2 * blocks16 <= cus && p.nk <= 128) return launch_s<D, CAUSAL, 16, 8>(p, stream);
+    return launch_prefill_f32_mfma(p, cus, stream);
 }
 
 template <int D>
@@ -240,8 +238,6 @@ hipError_t launch_d(const Problem& p, hipStream_t stream) {
 }
 
 }  // namespace
-
-static_assert(rows_of<4>() == kPrefillF32RowsPerBlock, "row tile mismatch");
 
 hipError_t launch_prefill_f32(const Problem& p, hipStream_t stream) {
     if (p.d == 64) return launch_d<64>(p, stream);
