@@ -13,13 +13,13 @@
 //
 // Three kernels:
 //  * bwd_rowdot: D_i from dO and O (fp32).
-//  * bwd_dq: one item = 256 queries of one (b, h); K and V stream through LDS
+//  * bwd_dq: one item = 128 or 256 queries of one (b, h); K and V stream through LDS
 //    in 64-key stages.  S^T = K Q^T and dP^T = V dO^T on the MFMA (K and V
 //    rows as A operands, Q and dO fragments held in registers as in the
 //    forward), dS^T in registers, dQ^T += K^T dS^T with K^T from transposing
 //    LDS reads of the same K stage.
-//  * bwd_dkdv_pair: one item = 128 keys of one (b, h); Q, dO, LSE and D
-//    stream through LDS in 64-query stages.  S = Q K^T and dP = dO V^T (Q and
+//  * bwd_dkdv_pair: one item = 64, 128 or 256 keys of one (b, h); Q, dO, LSE
+//    and D stream through LDS in stages of 32 or 64 queries.  S = Q K^T and dP = dO V^T (Q and
 //    dO rows as A operands, K or V fragments in registers), so a lane holds
 //    one key; dV^T += dO^T P and dK^T += Q^T dS with dO^T and Q^T from
 //    transposing reads.  The two halves of that work go to two waves of the
@@ -169,14 +169,19 @@ __device__ __forceinline__ void buffer_load16_to_lds_untracked(u32x4 rsrc, uint3
 // barrier): lane l of the i-th load of wave w fills slot S = (w*LPS + i)*64
 // + l of the stage, which holds logical chunk (S % CHUNKS) ^ swz(row) of row
 // S / CHUNKS (the forward's swizzled layout).
-template <int D, int NW>
+template <int D, int NW, int ROWS = BN>
 struct DmaStager {
-    static constexpr int LPS = Cfg<D>::TILE_BYTES / (NW * 1024);
-    static_assert(Cfg<D>::TILE_BYTES % (NW * 1024) == 0, "a stage must split into wave loads");
+    static constexpr int STAGE_BYTES = ROWS * Cfg<D>::ROW_BYTES;
+    static constexpr bool PART = STAGE_BYTES < NW * 1024;          // only the first waves load
+    static constexpr int LPS = PART ? 1 : STAGE_BYTES / (NW * 1024);
+    static_assert(STAGE_BYTES % 1024 == 0 && (PART || STAGE_BYTES % (NW * 1024) == 0),
+                  "a stage must split into wave loads");
+    bool on = true;          // this wave loads
     uint32_t goff[LPS];
     uint32_t lds_off;        // this wave's first 1 KB of a stage
     __device__ __forceinline__ DmaStager(int wave, int lane) {
         lds_off = (uint32_t)wave * LPS * 1024u;
+        if (PART) on = wave < STAGE_BYTES / 1024;
 #pragma unroll
         for (int i = 0; i < LPS; ++i) {
             const int slot = (wave * LPS + i) * 64 + lane;
@@ -187,7 +192,8 @@ struct DmaStager {
     // Rows j*64 .. j*64 + 63 of a head slice of `n` rows into `stage`; rows
     // past n are zero.
     __device__ __forceinline__ void issue(const u16* head, int n, int j, unsigned char* stage) const {
-        const int r0 = min(j * BN, n);
+        if (PART && !on) return;
+        const int r0 = min(j * ROWS, n);
         const u32x4 r = rsrc_words(head + (size_t)r0 * D, (uint32_t)(n - r0) * Cfg<D>::ROW_BYTES);
         const uint32_t base = lds_address(stage) + lds_off;
 #pragma unroll
@@ -215,35 +221,42 @@ __device__ __forceinline__ void store_rows16(void* out, size_t row_base, int hal
         }
 }
 
-// ---- dQ: 8 waves x 32 queries; K and V stages of 64 keys.
+// ---- dQ: 8 waves x 32 queries; K and V stages of 64 keys.  KS = 1: 256
+// queries per item, one key stream.  KS = 2: 128 queries, two key streams
+// (waves 4 .. 7 hold the queries of waves 0 .. 3 and take every second key
+// stage through a ring of their own); the partial sums of dQ meet in LDS.
+// The key loop runs over the stages of which a wave needs both 32-key steps,
+// without a test inside; the stage it needs half of, and those it only passes
+// through, follow in a loop of their own (B2 H16 4K d = 64 backward 545 -> 484
+// us, d = 128 causal 462 -> 452: the tests kept the steps from overlapping).
 constexpr int DQ_WAVES = 8;
 constexpr int DQ_THREADS = DQ_WAVES * 64;
-constexpr int DQ_BM = DQ_WAVES * 32;
 
-template <int D, bool CAUSAL, bool OUT_BF16>
+template <int D, bool CAUSAL, bool OUT_BF16, int KS>
 __global__ __launch_bounds__(DQ_THREADS, 1) void bwd_dq_kernel(
     const u16* __restrict__ Q, const u16* __restrict__ K, const u16* __restrict__ V,
     const u16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Dsum,
     void* __restrict__ dQ, int Nq, int Nk, int n_bh, int n_qtiles, float c, float scale) {
     using C = Cfg<D>;
     constexpr uint32_t RB = C::ROW_BYTES;
-    __shared__ __attribute__((aligned(1024))) unsigned char k_r0[C::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char k_r1[C::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_r0[C::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_r1[C::TILE_BYTES];
+    constexpr int QB = DQ_WAVES / KS;       // query blocks of 32
+    constexpr int BMQ = QB * 32;            // queries per item
+    __shared__ __attribute__((aligned(1024))) unsigned char k_r[2][KS][C::TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char v_r[2][KS][C::TILE_BYTES];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int qw = wave % QB, grp = wave / QB;   // query block, key stream
     const int col = lane & 31, half = lane >> 5;
     const int off = Nk - Nq;
     const TileAddr<D> ta(lane);
-    const DmaStager<D, DQ_WAVES> stg(wave, lane);
+    const DmaStager<D, QB> stg(qw, lane);
 
     for (int item = 0;; ++item) {
         int bh, qt;
         if (!item_of(blockIdx.x, item, gridDim.x, n_bh, n_qtiles, CAUSAL, bh, qt)) break;
-        const int q0 = qt * DQ_BM;
-        const int qrow = q0 + wave * 32 + col;
+        const int q0 = qt * BMQ;
+        const int qrow = q0 + qw * 32 + col;
         const u16* Kh = K + (size_t)bh * Nk * D;
         const u16* Vh = V + (size_t)bh * Nk * D;
 
@@ -262,13 +275,16 @@ __global__ __launch_bounds__(DQ_THREADS, 1) void bwd_dq_kernel(
         const float lse2 = row_ok ? LSE[(size_t)bh * Nq + qrow] * kLog2e : 0.0f;
         const float dsum = row_ok ? Dsum[(size_t)bh * Nq + qrow] : 0.0f;
 
-        const int kv_end = CAUSAL ? min(Nk, q0 + DQ_BM + off) : Nk;
+        const int kv_end = CAUSAL ? min(Nk, q0 + BMQ + off) : Nk;
         const int n_sub = (kv_end + SUB - 1) / SUB;
         const int n_stages = (n_sub + 1) / 2;
-        const int wave_q_first = q0 + wave * 32;
+        const int n_iter = (n_stages + KS - 1) / KS;
+        const int wave_q_first = q0 + qw * 32;
         int n_w = n_sub;
         if (wave_q_first >= Nq) n_w = 0;
         else if (CAUSAL) n_w = min(n_sub, (wave_q_first + 31 + off) / SUB + 1);
+        // Iterations in which this wave needs both steps of its stage.
+        const int n_full = max(0, (n_w / 2 - grp + KS - 1) / KS);
 
         f32x16 acc[D / 32];
 #pragma unroll
@@ -284,17 +300,18 @@ __global__ __launch_bounds__(DQ_THREADS, 1) void bwd_dq_kernel(
                 dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(stage_rows<D>(vs, ta, u, k), gf[k], dp, 0, 0, 0);
             }
             const int kbase = t * SUB;
-            const bool need_mask = (kbase + SUB > Nk) || (CAUSAL && kbase + SUB - 1 > wave_q_first + off);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = __builtin_fmaf(s[i], c, -lse2);
+            if ((kbase + SUB > Nk) || (CAUSAL && kbase + SUB - 1 > wave_q_first + off)) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int key = kbase + (i >> 2) * 8 + half * 4 + (i & 3);
+                    if (key >= Nk || (CAUSAL && key > qrow + off)) s[i] = kNegInf;
+                }
+            }
             float ds[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                float t = __builtin_fmaf(s[i], c, -lse2);
-                if (need_mask) {
-                    const int key = kbase + (i >> 2) * 8 + half * 4 + (i & 3);
-                    if (key >= Nk || (CAUSAL && key > qrow + off)) t = kNegInf;
-                }
-                ds[i] = exp2_hw(t) * (dp[i] - dsum);
-            }
+            for (int i = 0; i < 16; ++i) ds[i] = exp2_hw(s[i]) * (dp[i] - dsum);
             bf16x8 dsb[2];
             pack16(ds, dsb);
 #pragma unroll
@@ -305,45 +322,82 @@ __global__ __launch_bounds__(DQ_THREADS, 1) void bwd_dq_kernel(
                                                                      acc[b], 0, 0, 0);
         };
 
-        // Stage iteration j: K(j), V(j) in slot j & 1.  Right after the
-        // barrier the loads of K(j+1), V(j+1) start into the other slot,
+        // Iteration j: stage js = j * KS + grp in ring slot j & 1.  Right
+        // after the barrier the next stage's loads start into the other slot,
         // whose readers (iteration j - 1) are done; each wave waits for its
         // own loads before the next barrier.
-        stg.issue(Kh, Nk, 0, k_r0);
-        stg.issue(Vh, Nk, 0, v_r0);
-        for (int j = 0; j < n_stages; ++j) {
-            unsigned char* ks = (j & 1) ? k_r1 : k_r0;
-            unsigned char* vs = (j & 1) ? v_r1 : v_r0;
+        auto issue = [&](int j) __attribute__((always_inline)) {
+            stg.issue(Kh, Nk, j * KS + grp, k_r[j & 1][grp]);
+            stg.issue(Vh, Nk, j * KS + grp, v_r[j & 1][grp]);
+        };
+        auto advance = [&](int j) __attribute__((always_inline)) {
             wait_vmcnt<0>();
             wait_lgkmcnt0();
             barrier_no_fence();
-            if (j + 1 < n_stages) {
-                stg.issue(Kh, Nk, j + 1, (j & 1) ? k_r0 : k_r1);
-                stg.issue(Vh, Nk, j + 1, (j & 1) ? v_r0 : v_r1);
-            }
-            if (2 * j < n_w) step(ks, vs, 0, 2 * j);
-            if (2 * j + 1 < n_w) step(ks, vs, 1, 2 * j + 1);
+            if (j + 1 < n_iter) issue(j + 1);
+        };
+        issue(0);
+        int j = 0;
+        for (; j < n_full; ++j) {
+            advance(j);
+            const int js = j * KS + grp;
+            step(k_r[j & 1][grp], v_r[j & 1][grp], 0, 2 * js);
+            step(k_r[j & 1][grp], v_r[j & 1][grp], 1, 2 * js + 1);
+        }
+        for (; j < n_iter; ++j) {
+            advance(j);
+            const int js = j * KS + grp;
+            if (2 * js < n_w) step(k_r[j & 1][grp], v_r[j & 1][grp], 0, 2 * js);
         }
         wait_lgkmcnt0();
         barrier_no_fence();
-        if (row_ok) store_rows16<D, OUT_BF16>(dQ, ((size_t)bh * Nq + qrow) * D, half, acc, scale);
+        if constexpr (KS == 2) {
+            float* x = reinterpret_cast<float*>(qw < 2 ? &k_r[0][0][0] : &v_r[0][0][0]) + (qw & 1) * (D / 2) * 64;
+            if (grp == 1) {
+#pragma unroll
+                for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) x[(b * 16 + i) * 64 + lane] = acc[b][i];
+            }
+            __syncthreads();
+            if (grp == 0) {
+#pragma unroll
+                for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[b][i] += x[(b * 16 + i) * 64 + lane];
+            }
+            __syncthreads();   // the next item's stages land in the same LDS
+        }
+        if (row_ok && grp == 0) store_rows16<D, OUT_BF16>(dQ, ((size_t)bh * Nq + qrow) * D, half, acc, scale);
     }
 }
 
-// ---- dK, dV with two waves per SIMD: 8 waves, 128 keys per item.  Wave w
-// < 4 (role A) owns keys 32w .. 32w + 31 of the item for dV: S = Q K^T, the
-// weights P (exponentials), dV^T += dO^T P, and P handed to its partner
-// through LDS as bf16.  Wave w + 4 (role B, on the same SIMD) owns the same
-// keys for dK: dP = dO V^T, dS = P (dP - D) with the partner's P, dK^T +=
-// Q^T dS.  The matrix work of a step splits evenly between the two waves and
-// nothing is computed twice; B runs one 64-query stage behind A, so the LDS
-// ring holds three Q / dO stages and two stages of exchanged weights.
+// ---- dK, dV with two waves per SIMD.  A pair of waves (w, w + 4) owns 32 *
+// NKB keys.  Wave w < 4 (role A): S = Q K^T, the weights P (exponentials),
+// dV^T += dO^T P, and P handed to its partner through LDS as bf16.  Wave
+// w + 4 (role B, on the same SIMD): dP = dO V^T, dS = P (dP - D) with the
+// partner's P, dK^T += Q^T dS.  The matrix work of a step splits evenly
+// between the two waves and nothing is computed twice; B runs one stage of SR
+// queries behind A, so the LDS ring holds three Q / dO stages and two stages
+// of exchanged weights.
+//
+// Each role has a loop of its own.  With one loop and the role tested inside,
+// the compiler kept both roles' accumulators in one register set and copied
+// them at every join (249 registers, 64 moves a stage); apart, the same code
+// takes 236 with the operand reads further ahead, 16K causal d = 128 (dK, dV
+// kernel with dQ) 7.40 -> 6.69 ms, B2 H16 4K 512 -> 470 us.
+//
+// NKB = 2 (d = 64): every operand read from LDS feeds two products, B2 H16 4K
+// 551 -> 515 us.  At d = 128 the second key block does not fit the registers
+// (256, 5 reloads per step: 7.25 -> 8.35 ms).
+// QS = 2: two query streams for grids that leave compute units idle: pairs 0,
+// 1 and pairs 2, 3 own the same keys, each half takes every second stage
+// through a ring of its own, and the partial sums meet in LDS.
 constexpr int KV2_WAVES = 8;
 constexpr int KV2_THREADS = KV2_WAVES * 64;
-constexpr int KV2_BN = 4 * 32;   // keys per item
 constexpr int KV2_RING = 3;      // Q / dO stages in LDS
 
-template <int D, bool CAUSAL, bool OUT_BF16>
+template <int D, bool CAUSAL, bool OUT_BF16, int NKB, int SR, int QS>
 __global__ __launch_bounds__(KV2_THREADS, 1) void bwd_dkdv_pair_kernel(
     const u16* __restrict__ Q, const u16* __restrict__ K, const u16* __restrict__ V,
     const u16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Dsum,
@@ -351,19 +405,25 @@ __global__ __launch_bounds__(KV2_THREADS, 1) void bwd_dkdv_pair_kernel(
     float scale) {
     using C = Cfg<D>;
     constexpr uint32_t RB = C::ROW_BYTES;
-    __shared__ __attribute__((aligned(1024))) unsigned char q_r[KV2_RING][C::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char g_r[KV2_RING][C::TILE_BYTES];
-    // Exchanged weights: [stage parity][key block][32-query half][chunk c2][lane] x 16 bytes.
-    __shared__ __attribute__((aligned(1024))) uint4 p_x[2][4][2][2][64];
-    __shared__ __attribute__((aligned(16))) float l_r[KV2_RING][2][BN];   // [slot][lse2, D][query]
+    constexpr int KW = 32 * NKB;            // keys per pair of waves
+    constexpr int NP = 4 / QS;              // pairs side by side
+    constexpr int KT = NP * KW;             // keys per item
+    constexpr int U = SR / SUB;             // steps per stage
+    static_assert(U == 1 || (U == 2 && QS == 1), "a first odd step belongs to the only stream");
+    __shared__ __attribute__((aligned(1024))) unsigned char q_r[KV2_RING][QS][SR * C::ROW_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char g_r[KV2_RING][QS][SR * C::ROW_BYTES];
+    // Exchanged weights: [stage parity][wave pair][step][key block][chunk c2][lane] x 16 bytes.
+    __shared__ __attribute__((aligned(1024))) uint4 p_x[2][4][U][NKB][2][64];
+    __shared__ __attribute__((aligned(16))) float l_r[KV2_RING][QS][2][SR];   // [slot][stream][lse2, D][query]
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int role = wave >> 2, kb = wave & 3;   // role 0: P and dV; role 1: dS and dK
+    const int role = wave >> 2, pair = wave & 3;   // role 0: P and dV; role 1: dS and dK
+    const int kb = pair % NP, qs = pair / NP;      // key block, query stream
     const int col = lane & 31, half = lane >> 5;
     const int off = Nk - Nq;
-    const TileAddr<D> ta(lane);
-    const DmaStager<D, KV2_WAVES> stg(wave, lane);
+    TileAddr<D> ta(lane);
+    const DmaStager<D, KV2_WAVES / QS, SR> stg(role * NP + kb, lane);
 
     for (int item = 0;; ++item) {
         int bh, rt;
@@ -371,158 +431,250 @@ __global__ __launch_bounds__(KV2_THREADS, 1) void bwd_dkdv_pair_kernel(
         // Causal key tiles cost most at the start of the sequence: the
         // heaviest-first rank order of item_of is reversed here.
         const int kt = CAUSAL ? n_ktiles - 1 - rt : rt;
-        const int k0 = kt * KV2_BN;
-        const int krow = k0 + kb * 32 + col;
-        const bool key_ok = krow < Nk;
+        const int k0 = kt * KT;
+        const int blk_k_first = k0 + kb * KW;
         const u16* Qh = Q + (size_t)bh * Nq * D;
         const u16* Gh = dO + (size_t)bh * Nq * D;
         const float* Lh = LSE + (size_t)bh * Nq;
         const float* Dh = Dsum + (size_t)bh * Nq;
 
-        // K (role A) or V (role B) fragment of this lane's key: B operands.
-        bf16x8 kvf[D / 16];
+        // K (role A) or V (role B) fragments of this lane's keys: B operands.
+        bf16x8 kvf[NKB][D / 16];
         {
             const auto r = make_rsrc((role == 0 ? K : V) + (size_t)bh * Nk * D, (uint32_t)Nk * RB);
 #pragma unroll
-            for (int s = 0; s < D / 16; ++s)
-                kvf[s] = __builtin_bit_cast(bf16x8, buffer_load16(r, (uint32_t)krow * RB + s * 32 + half * 16));
+            for (int n = 0; n < NKB; ++n)
+#pragma unroll
+                for (int s = 0; s < D / 16; ++s)
+                    kvf[n][s] = __builtin_bit_cast(
+                        bf16x8, buffer_load16(r, (uint32_t)(blk_k_first + 32 * n + col) * RB + s * 32 + half * 16));
         }
 
         // Queries that see any key of the tile (query i sees key j iff
-        // j <= i + off), in 64-query stages; the block's first needed step.
+        // j <= i + off), in stages; the pair's first needed step.
         const int q_lo = CAUSAL ? max(0, k0 - off) : 0;
-        const int st0 = q_lo / BN;
-        const int n_stages = (Nq + BN - 1) / BN - st0;
-        const int blk_k_first = k0 + kb * 32;
+        const int st0 = q_lo / SR;
+        const int n_stages = ((Nq + SR - 1) / SR - st0 + QS - 1) / QS;   // of each stream
         const int t_first = CAUSAL ? max(0, blk_k_first - off) / SUB : 0;   // global 32-query step
         const bool blk_live = blk_k_first < Nk;
 
-        f32x16 acc[D / 32];          // dV^T (role A) or dK^T (role B)
+        f32x16 acc[NKB][D / 32];     // dV^T (role A) or dK^T (role B)
 #pragma unroll
-        for (int b = 0; b < D / 32; ++b) acc[b] = f32x16{};
+        for (int n = 0; n < NKB; ++n)
+#pragma unroll
+            for (int b = 0; b < D / 32; ++b) acc[n][b] = f32x16{};
 
-        // Role A, step u of stage js: weights of 32 queries x this lane's key.
+        // Role A, step u of stage js: weights of 32 queries x this lane's keys.
         auto step_a = [&](const unsigned char* qs, const unsigned char* gs, const float* ls, uint4* px,
                           int u, int t) __attribute__((always_inline)) {
-            f32x16 s = f32x16{};
+
+            f32x16 s[NKB];
 #pragma unroll
-            for (int k = 0; k < D / 16; ++k)
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(stage_rows<D>(qs, ta, u, k), kvf[k], s, 0, 0, 0);
-            const int qbase = t * SUB;
-            const bool need_mask = (qbase + SUB > Nq) || (CAUSAL && qbase < blk_k_first + 31 - off);
-            float p[16];
+            for (int n = 0; n < NKB; ++n) s[n] = f32x16{};
+#pragma unroll
+            for (int k = 0; k < D / 16; ++k) {
+                const bf16x8 a = stage_rows<D>(qs, ta, u, k);
+#pragma unroll
+                for (int n = 0; n < NKB; ++n)
+                    s[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kvf[n][k], s[n], 0, 0, 0);
+            }
+            // Exponents, then the mask (which must not pass through c).
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int m0 = 32 * u + 8 * g + 4 * half;   // stage-local query of element 4g
                 const float4 l4 = *reinterpret_cast<const float4*>(ls + m0);
                 const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = 4 * g + r;
-                    float x = __builtin_fmaf(s[i], c, -lv[r]);
-                    if (need_mask) {
-                        const int qi = qbase + 8 * g + 4 * half + r;
-                        if (qi >= Nq || (CAUSAL && krow > qi + off)) x = kNegInf;
-                    }
-                    p[i] = exp2_hw(x);
-                }
-            }
-            bf16x8 pb[2];
-            pack16(p, pb);
+                for (int n = 0; n < NKB; ++n)
 #pragma unroll
-            for (int c2 = 0; c2 < 2; ++c2) px[c2 * 64 + lane] = __builtin_bit_cast(uint4, pb[c2]);
+                    for (int r = 0; r < 4; ++r) s[n][4 * g + r] = __builtin_fmaf(s[n][4 * g + r], c, -lv[r]);
+            }
+            const int qbase = t * SUB;
+            if ((qbase + SUB > Nq) || (CAUSAL && qbase < blk_k_first + KW - 1 - off)) {
+#pragma unroll
+                for (int n = 0; n < NKB; ++n)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int qi = qbase + (i >> 2) * 8 + 4 * half + (i & 3);
+                        if (qi >= Nq || (CAUSAL && blk_k_first + 32 * n + col > qi + off)) s[n][i] = kNegInf;
+                    }
+            }
+            bf16x8 pb[NKB][2];
+#pragma unroll
+            for (int n = 0; n < NKB; ++n) {
+                float p[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) p[i] = exp2_hw(s[n][i]);
+                pack16(p, pb[n]);
+#pragma unroll
+                for (int c2 = 0; c2 < 2; ++c2) px[(n * 2 + c2) * 64 + lane] = __builtin_bit_cast(uint4, pb[n][c2]);
+            }
 #pragma unroll
             for (int c2 = 0; c2 < 2; ++c2)
 #pragma unroll
-                for (int b = 0; b < D / 32; ++b)
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(stage_tr<D>(gs, ta, b, 2 * u + c2), pb[c2],
-                                                                     acc[b], 0, 0, 0);
+                for (int b = 0; b < D / 32; ++b) {
+                    const bf16x8 a = stage_tr<D>(gs, ta, b, 2 * u + c2);
+#pragma unroll
+                    for (int n = 0; n < NKB; ++n)
+                        acc[n][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[n][c2], acc[n][b], 0, 0, 0);
+                }
         };
 
         // Role B, step u of stage js: dS from the partner's weights.
         auto step_b = [&](const unsigned char* qs, const unsigned char* gs, const float* dsv, const uint4* px,
                           int u) __attribute__((always_inline)) {
-            f32x16 dp = f32x16{};
+
+            f32x16 dp[NKB];
 #pragma unroll
-            for (int k = 0; k < D / 16; ++k)
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(stage_rows<D>(gs, ta, u, k), kvf[k], dp, 0, 0, 0);
-            const uint4 w0 = px[lane], w1 = px[64 + lane];
-            const uint32_t pw[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-            float ds[16];
+            for (int n = 0; n < NKB; ++n) dp[n] = f32x16{};
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int m0 = 32 * u + 8 * g + 4 * half;
-                const float4 d4 = *reinterpret_cast<const float4*>(dsv + m0);
-                const float dvv[4] = {d4.x, d4.y, d4.z, d4.w};
+            for (int k = 0; k < D / 16; ++k) {
+                const bf16x8 a = stage_rows<D>(gs, ta, u, k);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = 4 * g + r;
-                    const float pi = (i & 1) ? bf16hi_to_f32(pw[i >> 1]) : bf16lo_to_f32(pw[i >> 1]);
-                    ds[i] = pi * (dp[i] - dvv[r]);
-                }
+                for (int n = 0; n < NKB; ++n)
+                    dp[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kvf[n][k], dp[n], 0, 0, 0);
             }
-            bf16x8 dsb[2];
-            pack16(ds, dsb);
+            bf16x8 dsb[NKB][2];
+#pragma unroll
+            for (int n = 0; n < NKB; ++n) {
+                const uint4 w0 = px[(n * 2 + 0) * 64 + lane], w1 = px[(n * 2 + 1) * 64 + lane];
+                const uint32_t pw[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+                float ds[16];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int m0 = 32 * u + 8 * g + 4 * half;
+                    const float4 d4 = *reinterpret_cast<const float4*>(dsv + m0);
+                    const float dvv[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int i = 4 * g + r;
+                        const float pi = (i & 1) ? bf16hi_to_f32(pw[i >> 1]) : bf16lo_to_f32(pw[i >> 1]);
+                        ds[i] = pi * (dp[n][i] - dvv[r]);
+                    }
+                }
+                pack16(ds, dsb[n]);
+            }
 #pragma unroll
             for (int c2 = 0; c2 < 2; ++c2)
 #pragma unroll
-                for (int b = 0; b < D / 32; ++b)
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(stage_tr<D>(qs, ta, b, 2 * u + c2), dsb[c2],
-                                                                     acc[b], 0, 0, 0);
+                for (int b = 0; b < D / 32; ++b) {
+                    const bf16x8 a = stage_tr<D>(qs, ta, b, 2 * u + c2);
+#pragma unroll
+                    for (int n = 0; n < NKB; ++n)
+                        acc[n][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dsb[n][c2], acc[n][b], 0, 0, 0);
+                }
         };
 
-        // LSE and D of a stage's 64 queries: one float per lane of waves 0
-        // and 1 (zero past Nq), stored one iteration after the load.
+        // LSE and D of a stage's queries: one float per lane of the stream's
+        // first pair (zero past Nq), stored one iteration after the load.
         auto load_ld = [&](int js, float& x) __attribute__((always_inline)) {
-            const int qi = js * BN + lane;
+            const int qi = js * SR + lane;
             x = 0.0f;
-            if (wave < 2 && qi < Nq) x = (wave == 0) ? Lh[qi] : Dh[qi];
+            if (kb == 0 && lane < SR && qi < Nq) x = (role == 0) ? Lh[qi] : Dh[qi];
         };
 
-        // Iteration j: stage st0 + j is in the ring; role A works on it,
-        // role B on the stage before (whose weights A wrote in iteration
-        // j - 1).  Right after the barrier the loads of stage j + 1 start
-        // into the slot whose last reader (role B, iteration j - 1) is done,
-        // and each wave waits for its own loads before the next barrier.
+        // Iteration j: the stream's stage j (stage st0 + j * QS + qs of the
+        // sequence) is in the ring; role A works on it, role B on the stage
+        // before (whose weights A wrote in iteration j - 1).  Right after the
+        // barrier the loads of stage j + 1 start into the slot whose last
+        // reader (role B, iteration j - 1) is done, and each wave waits for
+        // its own loads before the next barrier.  A stream may have one stage
+        // less than the other: it walks an empty one (all rows past Nq).
+        auto seq = [&](int j) { return st0 + j * QS + qs; };
         float sx;
-        stg.issue(Qh, Nq, st0, q_r[0]);
-        stg.issue(Gh, Nq, st0, g_r[0]);
-        load_ld(st0, sx);
-        for (int j = 0; j <= n_stages; ++j) {
-            const int js = st0 + j;
-            const int slot = j % KV2_RING;
-            if (j < n_stages && wave < 2) l_r[slot][wave][lane] = (wave == 0) ? sx * kLog2e : sx;
+        stg.issue(Qh, Nq, seq(0), q_r[0][qs]);
+        stg.issue(Gh, Nq, seq(0), g_r[0][qs]);
+        load_ld(seq(0), sx);
+        int slot = 0;            // ring slot of stage j
+        auto advance = [&](int j) __attribute__((always_inline)) {
+            if (j < n_stages && kb == 0 && lane < SR) l_r[slot][qs][role][lane] = (role == 0) ? sx * kLog2e : sx;
             wait_vmcnt<0>();
             wait_lgkmcnt0();
             barrier_no_fence();
             if (j + 1 < n_stages) {
-                const int ns = (j + 1) % KV2_RING;
-                stg.issue(Qh, Nq, js + 1, q_r[ns]);
-                stg.issue(Gh, Nq, js + 1, g_r[ns]);
-                load_ld(js + 1, sx);
+                const int ns = (slot == KV2_RING - 1) ? 0 : slot + 1;
+                stg.issue(Qh, Nq, seq(j + 1), q_r[ns][qs]);
+                stg.issue(Gh, Nq, seq(j + 1), g_r[ns][qs]);
+                load_ld(seq(j + 1), sx);
             }
-            if (!blk_live) continue;
-            if (role == 0) {
-                if (j < n_stages) {
+        };
+        auto next_slot = [&]() __attribute__((always_inline)) { slot = (slot == KV2_RING - 1) ? 0 : slot + 1; };
+        // Stages before the pair's first visible query (all, for a pair past
+        // Nk) are only passed through; `odd`: so is the first step of the
+        // first stage.
+        const bool odd = U == 2 && (t_first & 1) && blk_live;
+        const int j0 = blk_live ? min(n_stages, (t_first / U - st0 - qs + QS - 1) / QS) : n_stages;
+        if (role == 0) {
+            int j = 0;
+            for (; j < j0; ++j) { advance(j); next_slot(); }
+            if (odd) {
+                advance(j);
+                step_a(q_r[slot][qs], g_r[slot][qs], l_r[slot][qs][0], &p_x[j & 1][pair][U - 1][0][0][0], U - 1,
+                       U * seq(j) + U - 1);
+                next_slot();
+                ++j;
+            }
+            for (; j < n_stages; ++j) {
+                advance(j);
 #pragma unroll
-                    for (int u = 0; u < 2; ++u)
-                        if (2 * js + u >= t_first)
-                            step_a(q_r[slot], g_r[slot], l_r[slot][0], &p_x[j & 1][kb][u][0][0], u, 2 * js + u);
-                }
-            } else if (j >= 1) {
-                const int ps = (j - 1) % KV2_RING;
+                for (int u = 0; u < U; ++u)
+                    step_a(q_r[slot][qs], g_r[slot][qs], l_r[slot][qs][0], &p_x[j & 1][pair][u][0][0][0], u,
+                           U * seq(j) + u);
+                next_slot();
+            }
+            advance(j);
+        } else {
+            int j = 0;
+            for (; j <= j0; ++j) { advance(j); next_slot(); }
+            if (odd) {
+                advance(j);
+                const int ps = (slot == 0) ? KV2_RING - 1 : slot - 1;
+                step_b(q_r[ps][qs], g_r[ps][qs], l_r[ps][qs][1], &p_x[(j - 1) & 1][pair][U - 1][0][0][0], U - 1);
+                next_slot();
+                ++j;
+            }
+            for (; j <= n_stages; ++j) {
+                advance(j);
+                const int ps = (slot == 0) ? KV2_RING - 1 : slot - 1;
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    if (2 * (js - 1) + u >= t_first)
-                        step_b(q_r[ps], g_r[ps], l_r[ps][1], &p_x[(j - 1) & 1][kb][u][0][0], u);
+                for (int u = 0; u < U; ++u)
+                    step_b(q_r[ps][qs], g_r[ps][qs], l_r[ps][qs][1], &p_x[(j - 1) & 1][pair][u][0][0][0], u);
+                next_slot();
             }
         }
         wait_lgkmcnt0();
         barrier_no_fence();
-        if (key_ok) {
+        if constexpr (QS == 2) {
+            constexpr int XB = NKB * (D / 2) * 64;   // floats of one wave's accumulators
+            static_assert(2 * XB * 4 <= KV2_RING * QS * SR * C::ROW_BYTES, "two waves' sums per ring");
+            float* x = reinterpret_cast<float*>(role == 0 ? &q_r[0][0][0] : &g_r[0][0][0]) + kb * XB;
+            if (qs == 1) {
+#pragma unroll
+                for (int n = 0; n < NKB; ++n)
+#pragma unroll
+                    for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) x[((n * (D / 32) + b) * 16 + i) * 64 + lane] = acc[n][b][i];
+            }
+            __syncthreads();
+            if (qs == 0) {
+#pragma unroll
+                for (int n = 0; n < NKB; ++n)
+#pragma unroll
+                    for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) acc[n][b][i] += x[((n * (D / 32) + b) * 16 + i) * 64 + lane];
+            }
+            __syncthreads();   // the next item's stages land in the same LDS
+            if (qs == 1) continue;
+        }
+#pragma unroll
+        for (int n = 0; n < NKB; ++n) {
+            const int krow = blk_k_first + 32 * n + col;
+            if (krow >= Nk) continue;
             const size_t base = ((size_t)bh * Nk + krow) * D;
-            if (role == 0) store_rows16<D, OUT_BF16>(dV, base, half, acc, 1.0f);
-            else store_rows16<D, OUT_BF16>(dK, base, half, acc, scale);
+            if (role == 0) store_rows16<D, OUT_BF16>(dV, base, half, acc[n], 1.0f);
+            else store_rows16<D, OUT_BF16>(dK, base, half, acc[n], scale);
         }
     }
 }
@@ -533,6 +685,66 @@ int resident_per_cu(Kern kernel, int threads) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, 0) != hipSuccess) n = 1;
     return n > 0 ? n : 1;
 }
+
+template <int D, bool CAUSAL, bool OUT_BF16, int KS>
+hipError_t launch_dq(const BwdProblem& p, int cus, hipStream_t stream) {
+    auto kernel = bwd_dq_kernel<D, CAUSAL, OUT_BF16, KS>;
+    static const int per_cu = resident_per_cu(kernel, DQ_THREADS);
+    const int n_qt = (p.nq + 256 / KS - 1) / (256 / KS);
+    const long long items = (long long)p.bh * n_qt;
+    const unsigned grid = (unsigned)std::min<long long>(items, (long long)cus * per_cu);
+    return launch_kernel(kernel, dim3(grid), dim3(DQ_THREADS), stream, static_cast<const u16*>(p.q),
+                         static_cast<const u16*>(p.k), static_cast<const u16*>(p.v),
+                         static_cast<const u16*>(p.dout), p.lse, static_cast<const float*>(p.dsum),
+                         p.dq, p.nq, p.nk, p.bh, n_qt, p.scale * kLog2e, p.scale);
+}
+
+template <int D, bool CAUSAL, bool OUT_BF16, int NKB, int SR, int QS>
+hipError_t launch_dkdv(const BwdProblem& p, int cus, hipStream_t stream) {
+    auto kernel = bwd_dkdv_pair_kernel<D, CAUSAL, OUT_BF16, NKB, SR, QS>;
+    static const int per_cu = resident_per_cu(kernel, KV2_THREADS);
+    constexpr int KT = 128 * NKB / QS;
+    const int n_kt = (p.nk + KT - 1) / KT;
+    const long long items = (long long)p.bh * n_kt;
+    const unsigned grid = (unsigned)std::min<long long>(items, (long long)cus * per_cu);
+    return launch_kernel(kernel, dim3(grid), dim3(KV2_THREADS), stream, static_cast<const u16*>(p.q),
+                         static_cast<const u16*>(p.k), static_cast<const u16*>(p.v),
+                         static_cast<const u16*>(p.dout), p.lse, static_cast<const float*>(p.dsum),
+                         p.dk, p.dv, p.nq, p.nk, p.bh, n_kt, p.scale * kLog2e, p.scale);
+}
+
+// Choice of item size, by the items the busiest compute unit gets (`rounds`)
+// and, under the causal mask, where the snake deal evens them out, by whether
+// every unit gets one.  Backward calls, us, one box (MI355X, 256 units):
+//
+//   dQ                                 256-query items  128-query items, 2 key streams
+//   B4 H8 1000, d = 64 (128 / 256)          59.7            44.7
+//   B2 H8 1500, d = 128 (96 / 192)          101             81.8
+//   same, causal                            100             80.0
+//   B4 H12 2K, d = 128 (384 / 768)          353             345
+//   B4 H16 1K, d = 64 (256 / 512)           78.9            81.4
+//   B4 H12 2K causal, d = 64 (384 / 768)    124             128
+//   16K causal, B1 H32, d = 128             6610            6840
+//
+// A 128-query item costs about 11/20 of a 256-query one.
+//
+//   dK, dV                             128-key items    64-key items, 2 query streams
+//   B1 H8 1K, d = 128 (64 / 128)            58.5            50.0
+//   B1 H4 2K causal, d = 64 (64 / 128)      64.9            53.1
+//   B2 H8 1500 causal, d = 128 (192 / 384)  80.2            68.1
+//   B2 H8 1500, d = 128 (192 / 384)         82.9            97.4
+//   B1 H20 1K, d = 64 (160 / 320)           40.2            46.7
+//   B1 H5 8K causal, d = 128 (320 / 640)    366             363
+//
+//   dK, dV, d = 64                     128-key items    256-key items (NKB = 2)
+//   B2 H16 4K (1024 / 512)                  488             449
+//   B4 H16 1K (512 / 256)                   78.9            72.2
+//   B4 H12 2K causal (768 / 384)            124             119
+//   B4 H16 700 causal (384 / 192)           42.9            51.0
+//   B4 H8 1000 (256 / 128)                  49.7            59.7
+//
+// A 256-key item costs about 18/10 of a 128-key one.
+long long rounds(long long items, int cus) { return (items + cus - 1) / cus; }
 
 template <int D, bool CAUSAL, bool OUT_BF16>
 hipError_t launch(const BwdProblem& p, hipStream_t stream) {
@@ -548,33 +760,21 @@ hipError_t launch(const BwdProblem& p, hipStream_t stream) {
                      : launch_kernel(bwd_rowdot_kernel<D, false>, dim3(grid), dim3(256), stream,
                                      static_cast<const u16*>(p.dout), p.o, p.dsum, rows);
         if (e != hipSuccess) return e;
-    }
-    const float c = p.scale * kLog2e;
-    if (rows > 0) {
-        auto kernel = bwd_dq_kernel<D, CAUSAL, OUT_BF16>;
-        static const int per_cu = resident_per_cu(kernel, DQ_THREADS);
-        const int n_qt = (p.nq + DQ_BM - 1) / DQ_BM;
-        const long long items = (long long)p.bh * n_qt;
-        const unsigned grid = (unsigned)std::min<long long>(items, (long long)cus * per_cu);
-        e = launch_kernel(kernel, dim3(grid), dim3(DQ_THREADS), stream, static_cast<const u16*>(p.q),
-                          static_cast<const u16*>(p.k), static_cast<const u16*>(p.v),
-                          static_cast<const u16*>(p.dout), p.lse, static_cast<const float*>(p.dsum),
-                          p.dq, p.nq, p.nk, p.bh, n_qt, c, p.scale);
+        const long long i1 = (long long)p.bh * ((p.nq + 255) / 256), i2 = (long long)p.bh * ((p.nq + 127) / 128);
+        const bool split = CAUSAL ? i1 < cus : 20 * rounds(i1, cus) > 11 * rounds(i2, cus);
+        e = split ? launch_dq<D, CAUSAL, OUT_BF16, 2>(p, cus, stream)
+                  : launch_dq<D, CAUSAL, OUT_BF16, 1>(p, cus, stream);
         if (e != hipSuccess) return e;
     }
     // dK, dV (zero when there are no queries)
-    {
-        auto kernel = bwd_dkdv_pair_kernel<D, CAUSAL, OUT_BF16>;
-        static const int per_cu = resident_per_cu(kernel, KV2_THREADS);
-        const int n_kt = (p.nk + KV2_BN - 1) / KV2_BN;
-        const long long items = (long long)p.bh * n_kt;
-        const unsigned grid = (unsigned)std::min<long long>(items, (long long)cus * per_cu);
-        e = launch_kernel(kernel, dim3(grid), dim3(KV2_THREADS), stream, static_cast<const u16*>(p.q),
-                          static_cast<const u16*>(p.k), static_cast<const u16*>(p.v),
-                          static_cast<const u16*>(p.dout), p.lse, static_cast<const float*>(p.dsum),
-                          p.dk, p.dv, p.nq, p.nk, p.bh, n_kt, c, p.scale);
+    const long long k1 = (long long)p.bh * ((p.nk + 127) / 128);
+    if (CAUSAL ? k1 < cus : 2 * k1 <= cus) return launch_dkdv<D, CAUSAL, OUT_BF16, 1, 32, 2>(p, cus, stream);
+    if constexpr (D == 64) {
+        const long long k2 = (long long)p.bh * ((p.nk + 255) / 256);
+        if (CAUSAL ? k2 >= cus : 18 * rounds(k2, cus) <= 10 * rounds(k1, cus))
+            return launch_dkdv<D, CAUSAL, OUT_BF16, 2, 64, 1>(p, cus, stream);
     }
-    return e;
+    return launch_dkdv<D, CAUSAL, OUT_BF16, 1, 64, 1>(p, cus, stream);
 }
 
 template <int D>

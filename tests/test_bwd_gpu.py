@@ -171,6 +171,26 @@ def test_bwd_many_items_selected_heads():
         _check(tuple(g[sl] for g in got), ref, _bounds(qs, ks, vs, gs, scale, True), TOL_ISOLATED)
 
 
+# Item sizes by grid (256 compute units): 256 heads of at most 256 rows take 256-query items without
+# the mask (128-query ones under it), 256-key items at d = 64 and 128-key items at d = 128; 16 heads
+# of 600 take 128-query items in two key streams with 128-key items (without the mask) or 64-key
+# items in two query streams (with it).  Lengths one past a tile, odd first steps, Nq < Nk.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("shape,scale", [((8, 32, 129, 129, 64), 0.125), ((8, 32, 97, 130, 64), -0.2),
+                                         ((8, 32, 130, 257, 64), 0.125), ((8, 32, 129, 161, 128), 0.09),
+                                         ((4, 4, 577, 609, 128), 0.09), ((4, 4, 609, 641, 64), 0.0)])
+def test_bwd_item_sizes(shape, scale, causal):
+    B, H, Nq, Nk, d = shape
+    q, k, v, do = _inputs(B, H, Nq, Nk, d, _seed("items", shape, causal))
+    o, lse = oracle.attention(q, k, v, scale=scale, causal=causal, with_lse=True)
+    got = _gpu_bwd(q, k, v, do, o, lse, scale, causal)
+    for b, h in ((0, 0), (B - 1, H - 1), (B // 2, 1)):
+        sl = (slice(b, b + 1), slice(h, h + 1))
+        qs, ks, vs, gs = (a[sl] for a in (q, k, v, do))
+        ref = oracle.attention_bwd(qs, ks, vs, gs, scale=scale, causal=causal)
+        _check(tuple(g[sl] for g in got), ref, _bounds(qs, ks, vs, gs, scale, causal), TOL_ISOLATED)
+
+
 def test_bwd_deterministic():
     B, H, Nq, Nk, d = 1, 4, 600, 600, 128
     q, k, v, do = _inputs(B, H, Nq, Nk, d, _seed("det"))
