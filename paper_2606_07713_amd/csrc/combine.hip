@@ -19,7 +19,14 @@ constexpr int ROWS_PER_BLOCK = 4;   // one wave per query row
 
 // ws_acc: [rows][splits][D] fp32, ws_ml: [rows][splits][2] fp32 (m, l), with
 // row = bh * nq + i.  O is written through the layout's strides.
-template <int D, bool OUT_BF16>
+//
+// The pass is a chain of load latencies, not of bytes (a decode call of 32
+// rows x 8 splits reads 132 KB), so a row's splits are taken U at a time with
+// all of their loads in flight together and merged online: one latency per U
+// splits, where a loop over the splits for M and another for the sums paid
+// several per split.  B1 H32 Nk 4097 d = 128 (8 splits): the whole decode call
+// 19.3 -> 16.9 us; B1 H8 Nk 16000 (32 splits): 24.1 -> 17.1.
+template <int D, bool OUT_BF16, int U>
 __global__ __launch_bounds__(ROWS_PER_BLOCK * 64) void split_combine_kernel(
     const float* __restrict__ ws_acc, const float* __restrict__ ws_ml, void* __restrict__ Out,
     float* __restrict__ LSE, long long rows, int nq, int splits, Layout lay) {
@@ -29,17 +36,42 @@ __global__ __launch_bounds__(ROWS_PER_BLOCK * 64) void split_combine_kernel(
     if (row >= rows) return;
     const float* ml = ws_ml + (size_t)row * splits * 2;
     const float* ac = ws_acc + (size_t)row * splits * D;
-    float M = kNegInf;
-    for (int s = 0; s < splits; ++s) M = fmaxf(M, ml[2 * s]);
-    float L = 0.0f, o[PER];
+    float M = kNegInf, L = 0.0f, o[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) o[e] = 0.0f;
-    for (int s = 0; s < splits; ++s) {
-        const float ms = ml[2 * s];
-        const float w = (ms == kNegInf) ? 0.0f : exp2_hw(ms - M);
-        L += w * ml[2 * s + 1];
+    for (int s0 = 0; s0 < splits; s0 += U) {
+        float ms[U], ls[U], a[U][PER];
 #pragma unroll
-        for (int e = 0; e < PER; ++e) o[e] += w * ac[(size_t)s * D + e * 64 + lane];
+        for (int u = 0; u < U; ++u) {
+            const int s = min(s0 + u, splits - 1);
+            ms[u] = ml[2 * s];
+            ls[u] = ml[2 * s + 1];
+#pragma unroll
+            for (int e = 0; e < PER; ++e) a[u][e] = ac[(size_t)s * D + e * 64 + lane];
+        }
+        float m_new = M;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u >= splits) {   // past the last split: nothing, whatever it holds
+                ms[u] = kNegInf;
+                ls[u] = 0.0f;
+#pragma unroll
+                for (int e = 0; e < PER; ++e) a[u][e] = 0.0f;
+            }
+            m_new = fmaxf(m_new, ms[u]);
+        }
+        const float alpha = (M == kNegInf) ? 0.0f : exp2_hw(M - m_new);
+        M = m_new;
+        L *= alpha;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) o[e] *= alpha;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float w = (ms[u] == kNegInf) ? 0.0f : exp2_hw(ms[u] - M);
+            L += w * ls[u];
+#pragma unroll
+            for (int e = 0; e < PER; ++e) o[e] += w * a[u][e];
+        }
     }
     const float inv = 1.0f / L;
     const int bh = (int)(row / nq);
@@ -60,11 +92,14 @@ hipError_t launch_d(const Problem& p, int splits, const float* ws_acc, const flo
                     hipStream_t stream) {
     const long long rows = (long long)p.bh * p.nq;
     const unsigned grid = (unsigned)((rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK);
-    if (p.out_bf16)
-        return launch_kernel(split_combine_kernel<D, true>, dim3(grid), dim3(ROWS_PER_BLOCK * 64),
-                             stream, ws_acc, ws_ml, p.o, p.lse, rows, p.nq, splits, p.lay);
-    return launch_kernel(split_combine_kernel<D, false>, dim3(grid), dim3(ROWS_PER_BLOCK * 64),
-                         stream, ws_acc, ws_ml, p.o, p.lse, rows, p.nq, splits, p.lay);
+    const auto go = [&](auto kernel) {
+        return launch_kernel(kernel, dim3(grid), dim3(ROWS_PER_BLOCK * 64), stream, ws_acc, ws_ml, p.o,
+                             p.lse, rows, p.nq, splits, p.lay);
+    };
+    // Few splits take the narrow form: its spare loads would repeat the last split.
+    if (splits <= 4)
+        return p.out_bf16 ? go(split_combine_kernel<D, true, 4>) : go(split_combine_kernel<D, false, 4>);
+    return p.out_bf16 ? go(split_combine_kernel<D, true, 8>) : go(split_combine_kernel<D, false, 8>);
 }
 
 }  // namespace

@@ -13,12 +13,11 @@
 // Only the partial states (O(B*H*splits*dv)) and O itself are written.
 #include "device_common.h"
 #include "launch.h"
+#include "prefill_bf16_common.h"
 
 namespace moa {
 namespace {
 
-constexpr int WAVES = 4;
-constexpr int THREADS = WAVES * 64;
 constexpr int U = 8;   // 16-byte K (and V) loads per lane in flight per iteration
 
 template <typename T, int D>
@@ -69,8 +68,10 @@ __device__ __forceinline__ void merge_xor(float& m, float& l, float (&acc)[EPL])
 // O = acc / l (and LSE) itself -- the value the combine pass would compute
 // from a single split, where every merge weight is exactly 1 -- instead of
 // the partial state, and no combine pass runs.
-template <typename T, int D, bool DIRECT = false, bool OUT_BF16 = false>
-__global__ __launch_bounds__(THREADS) void decode_split_kernel(
+// WAVES: 4, or 8 for short chunks on grids of at most one workgroup per
+// compute unit (see launch_t).
+template <typename T, int D, int WAVES, bool DIRECT = false, bool OUT_BF16 = false>
+__global__ __launch_bounds__(WAVES * 64) void decode_split_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     float* __restrict__ ws_acc, float* __restrict__ ws_ml, int Nk, int splits,
     int keys_per_split, float c, Layout L, void* __restrict__ Out, float* __restrict__ LSE) {
@@ -195,16 +196,28 @@ hipError_t launch_t(const Problem& p, int splits, float* ws, hipStream_t stream)
     float* ws_acc = ws;
     float* ws_ml = ws + (size_t)p.bh * splits * D;
     const long long blocks = (long long)p.bh * splits;
-    const auto args = [&](auto kernel) {
-        return launch_kernel(kernel, dim3((unsigned)blocks), dim3(THREADS), stream,
+    const auto args = [&](auto kernel, int waves) {
+        return launch_kernel(kernel, dim3((unsigned)blocks), dim3(waves * 64), stream,
                              static_cast<const T*>(p.q), static_cast<const T*>(p.k),
                              static_cast<const T*>(p.v), ws_acc, ws_ml, p.nk, splits, kps,
                              p.scale * kLog2e, p.lay, p.o, p.lse);
     };
     if (splits == 1)
-        return p.out_bf16 ? args(decode_split_kernel<T, D, true, true>)
-                          : args(decode_split_kernel<T, D, true, false>);
-    const hipError_t e = args(decode_split_kernel<T, D>);
+        return p.out_bf16 ? args(decode_split_kernel<T, D, 4, true, true>, 4)
+                          : args(decode_split_kernel<T, D, 4, true, false>, 4);
+    // A wave's iterations over its chunk are a chain of memory latencies.  On
+    // a grid of at most one workgroup per compute unit, 8 waves walk a chunk
+    // of up to two of their iterations (512 keys at d = 128 in bf16) in half
+    // the links: B1 H32 Nk 4097 16.9 -> 16.0 us, Nk 1000 9.5 -> 8.8.  Longer
+    // chunks have enough loads in flight with 4 waves, which then lose less
+    // to the merge (B1 H32 Nk 16384: 43.3 us against 45.1 with 8), and grids
+    // beyond the compute units gain nothing (B3 H20 Nk 3000 d = 64: 14.6
+    // against 14.9).
+    int cus = 0;
+    hipError_t e = pf::device_cus(stream, cus);
+    if (e != hipSuccess) return e;
+    const bool wide = blocks <= cus && kps <= 2 * 8 * Cfg<T, D>::STEP;
+    e = wide ? args(decode_split_kernel<T, D, 8>, 8) : args(decode_split_kernel<T, D, 4>, 4);
     if (e != hipSuccess) return e;
     // a9: exact merge of the per-chunk states (one query row per batch*head).
     return launch_split_combine(p, splits, ws_acc, ws_ml, stream);

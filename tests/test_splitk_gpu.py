@@ -110,3 +110,28 @@ def test_fp32_prefill_ignores_split_request():
     q, k, v = gen(B, H, Nq, Nk, d, "f32", seed=_seed("f32"))
     o = run_gpu(q, k, v, causal=True, num_splits=4)
     assert max_err(o, oracle_full(q, k, v, causal=True)) <= TOL["f32"]
+
+
+# The combine pass takes splits four (up to 4 of them) or eight at a time, and decode runs four or
+# eight waves per chunk: edges of both, tolerance as everywhere.
+@pytest.mark.parametrize("splits", [2, 4, 5, 8, 9, 17])
+@pytest.mark.parametrize("nk_per_split", [31, 512, 513])
+def test_decode_chunk_and_combine_edges(splits, nk_per_split):
+    B, H, d = 1, 3, 128
+    Nk = splits * nk_per_split - 1
+    q, k, v = gen(B, H, 1, Nk, d, "bf16", seed=_seed("edges", splits, nk_per_split))
+    o, lse = run_gpu(q, k, v, out_dtype="f32", num_splits=splits, return_lse=True)
+    ref, ref_lse = oracle_full(q, k, v, with_lse=True)
+    assert max_err(o, ref) <= TOL["bf16"]
+    assert max_err(lse, ref_lse) <= _lse_tol(ref_lse)
+
+
+def test_combine_keeps_infinities():
+    # An infinite value reaches the output as itself: the spare slots of the combine's last
+    # group of splits contribute nothing rather than 0 * inf.
+    import torch
+    q, k, v = (torch.randn((1, 2, n, 64), device="cuda").bfloat16() for n in (1, 3000, 3000))
+    v[:, :, 2990, 5] = float("inf")
+    o = moa.attn_fwd(q, k, v, num_splits=5)
+    assert torch.isposinf(o[..., 5]).all()
+    assert torch.isfinite(o[..., :5]).all() and torch.isfinite(o[..., 6:]).all()
