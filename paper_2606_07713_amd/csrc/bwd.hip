@@ -11,10 +11,10 @@
 //   dV_j  = sum_i P_ij dO_i
 // which is the chain rule through the softmax the paper leaves to its Stage 5.
 //
-// Three kernels:
-//  * bwd_rowdot: D_i from dO and O (fp32).
-//  * bwd_dq: one item = 128 or 256 queries of one (b, h); K and V stream through LDS
-//    in 64-key stages.  S^T = K Q^T and dP^T = V dO^T on the MFMA (K and V
+// Two kernels:
+//  * bwd_dq: one item = 128 or 256 queries of one (b, h).  D_i of its queries from
+//    the dO fragments and O (fp32), kept and written out for the other kernel;
+//    then K and V stream through LDS in 64-key stages.  S^T = K Q^T and dP^T = V dO^T on the MFMA (K and V
 //    rows as A operands, Q and dO fragments held in registers as in the
 //    forward), dS^T in registers, dQ^T += K^T dS^T with K^T from transposing
 //    LDS reads of the same K stage.
@@ -42,43 +42,6 @@ namespace {
 using namespace pf;
 
 constexpr int SUB = 32;   // queries (bwd_dkdv) or keys (bwd_dq) per step
-
-// ---- D_i = <dO_i, O_i>: 16 lanes per row (8 elements each), 4 rows per wave.
-template <int D, bool O_BF16>
-__global__ __launch_bounds__(256) void bwd_rowdot_kernel(const u16* __restrict__ dO,
-                                                         const void* __restrict__ O,
-                                                         float* __restrict__ Dsum, long long rows) {
-    constexpr int LPR = D / 8;
-    const long long row = (long long)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-    const int e0 = (threadIdx.x % LPR) * 8;
-    float acc = 0.0f;
-    if (row < rows) {
-        const uint4 g = *reinterpret_cast<const uint4*>(dO + row * D + e0);
-        const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
-        float o[8];
-        if (O_BF16) {
-            const uint4 h = *reinterpret_cast<const uint4*>(static_cast<const u16*>(O) + row * D + e0);
-            const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                o[2 * j] = __uint_as_float(hw[j] << 16);
-                o[2 * j + 1] = __uint_as_float(hw[j] & 0xffff0000u);
-            }
-        } else {
-            const float4 a = *reinterpret_cast<const float4*>(static_cast<const float*>(O) + row * D + e0);
-            const float4 b = *reinterpret_cast<const float4*>(static_cast<const float*>(O) + row * D + e0 + 4);
-            o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w; o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            acc = __builtin_fmaf(__uint_as_float(gw[j] << 16), o[2 * j], acc);
-            acc = __builtin_fmaf(__uint_as_float(gw[j] & 0xffff0000u), o[2 * j + 1], acc);
-        }
-    }
-#pragma unroll
-    for (int m = 1; m < LPR; m <<= 1) acc += __shfl_xor(acc, m);
-    if (row < rows && (threadIdx.x % LPR) == 0) Dsum[row] = acc;
-}
 
 // Per-lane LDS addresses shared by both kernels (the stage layout of the
 // forward: 64 rows of D bf16, 16-byte chunks XOR-swizzled per row).
@@ -229,14 +192,19 @@ __device__ __forceinline__ void store_rows16(void* out, size_t row_base, int hal
 // without a test inside; the stage it needs half of, and those it only passes
 // through, follow in a loop of their own (B2 H16 4K d = 64 backward 545 -> 484
 // us, d = 128 causal 462 -> 452: the tests kept the steps from overlapping).
+//
+// D is formed in the prologue, where the dO fragments are in registers anyway:
+// a kernel of its own read dO once more and cost a launch, 12.6 us on B2 H16 4K
+// d = 128 and 3.7 on B4 H8 1000 d = 64 (training step 60.5 -> 55.5 us; the
+// same sums in the same order).
 constexpr int DQ_WAVES = 8;
 constexpr int DQ_THREADS = DQ_WAVES * 64;
 
 template <int D, bool CAUSAL, bool OUT_BF16, int KS>
 __global__ __launch_bounds__(DQ_THREADS, 1) void bwd_dq_kernel(
     const u16* __restrict__ Q, const u16* __restrict__ K, const u16* __restrict__ V,
-    const u16* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Dsum,
-    void* __restrict__ dQ, int Nq, int Nk, int n_bh, int n_qtiles, float c, float scale) {
+    const u16* __restrict__ dO, const void* __restrict__ O, int o_bf16,
+    const float* __restrict__ LSE, float* __restrict__ Dsum, void* __restrict__ dQ, int Nq, int Nk, int n_bh, int n_qtiles, float c, float scale) {
     using C = Cfg<D>;
     constexpr uint32_t RB = C::ROW_BYTES;
     constexpr int QB = DQ_WAVES / KS;       // query blocks of 32
@@ -273,7 +241,45 @@ __global__ __launch_bounds__(DQ_THREADS, 1) void bwd_dq_kernel(
         }
         const bool row_ok = qrow < Nq;
         const float lse2 = row_ok ? LSE[(size_t)bh * Nq + qrow] * kLog2e : 0.0f;
-        const float dsum = row_ok ? Dsum[(size_t)bh * Nq + qrow] : 0.0f;
+        // D of this lane's query: 8 elements at a time, then pairwise (the two
+        // halves of a 16-element chunk sit in lanes l and l ^ 32).
+        float dsum;
+        {
+            float part[D / 16];
+            const size_t o0 = ((size_t)bh * Nq + (row_ok ? qrow : 0)) * D + half * 8;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) {
+                float o[8];
+                if (o_bf16) {
+                    const uint4 h = *reinterpret_cast<const uint4*>(static_cast<const u16*>(O) + o0 + s * 16);
+                    const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        o[2 * j] = bf16lo_to_f32(hw[j]);
+                        o[2 * j + 1] = bf16hi_to_f32(hw[j]);
+                    }
+                } else {
+                    const float* of = static_cast<const float*>(O) + o0 + s * 16;
+                    const float4 x = *reinterpret_cast<const float4*>(of), y = *reinterpret_cast<const float4*>(of + 4);
+                    o[0] = x.x; o[1] = x.y; o[2] = x.z; o[3] = x.w;
+                    o[4] = y.x; o[5] = y.y; o[6] = y.z; o[7] = y.w;
+                }
+                const u32x4 g = __builtin_bit_cast(u32x4, gf[s]);
+                part[s] = 0.0f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    part[s] = __builtin_fmaf(bf16lo_to_f32(g[j]), o[2 * j], part[s]);
+                    part[s] = __builtin_fmaf(bf16hi_to_f32(g[j]), o[2 * j + 1], part[s]);
+                }
+                part[s] = half_sum(part[s]);
+            }
+#pragma unroll
+            for (int m = 1; m < D / 16; m <<= 1)
+#pragma unroll
+                for (int s = 0; s < D / 16; s += 2 * m) part[s] += part[s + m];
+            dsum = row_ok ? part[0] : 0.0f;
+            if (row_ok && half == 0 && grp == 0) Dsum[(size_t)bh * Nq + qrow] = dsum;
+        }
 
         const int kv_end = CAUSAL ? min(Nk, q0 + BMQ + off) : Nk;
         const int n_sub = (kv_end + SUB - 1) / SUB;
@@ -695,7 +701,7 @@ hipError_t launch_dq(const BwdProblem& p, int cus, hipStream_t stream) {
     const unsigned grid = (unsigned)std::min<long long>(items, (long long)cus * per_cu);
     return launch_kernel(kernel, dim3(grid), dim3(DQ_THREADS), stream, static_cast<const u16*>(p.q),
                          static_cast<const u16*>(p.k), static_cast<const u16*>(p.v),
-                         static_cast<const u16*>(p.dout), p.lse, static_cast<const float*>(p.dsum),
+                         static_cast<const u16*>(p.dout), p.o, p.o_bf16 ? 1 : 0, p.lse, p.dsum,
                          p.dq, p.nq, p.nk, p.bh, n_qt, p.scale * kLog2e, p.scale);
 }
 
@@ -751,15 +757,8 @@ hipError_t launch(const BwdProblem& p, hipStream_t stream) {
     int cus = 0;
     hipError_t e = device_cus(stream, cus);
     if (e != hipSuccess) return e;
-    const long long rows = (long long)p.bh * p.nq;
-    // D_i, then dQ (both have nothing to do without queries)
-    if (rows > 0) {
-        const unsigned grid = (unsigned)((rows + (256 / (D / 8)) - 1) / (256 / (D / 8)));
-        e = p.o_bf16 ? launch_kernel(bwd_rowdot_kernel<D, true>, dim3(grid), dim3(256), stream,
-                                     static_cast<const u16*>(p.dout), p.o, p.dsum, rows)
-                     : launch_kernel(bwd_rowdot_kernel<D, false>, dim3(grid), dim3(256), stream,
-                                     static_cast<const u16*>(p.dout), p.o, p.dsum, rows);
-        if (e != hipSuccess) return e;
+    // D and dQ (both have nothing to do without queries)
+    if (p.bh > 0 && p.nq > 0) {
         const long long i1 = (long long)p.bh * ((p.nq + 255) / 256), i2 = (long long)p.bh * ((p.nq + 127) / 128);
         const bool split = CAUSAL ? i1 < cus : 20 * rounds(i1, cus) > 11 * rounds(i2, cus);
         e = split ? launch_dq<D, CAUSAL, OUT_BF16, 2>(p, cus, stream)

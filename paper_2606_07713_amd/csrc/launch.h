@@ -102,7 +102,7 @@ struct BwdProblem {
     bool grad_bf16;
 };
 
-// Backward: row-dot kernel (D), dQ kernel, dK/dV kernel, in stream order.
+// Backward: dQ kernel (with D), dK/dV kernel, in stream order.
 hipError_t launch_bwd(const BwdProblem& p, hipStream_t stream);
 
 // Bytes of the fixed device scratch array of moa_attn_fwd_noalloc (one per
