@@ -149,3 +149,31 @@ def test_projected_forward_full_size_sampled():
     say(f"  max err {err:.3e}")
     assert err <= TOL["bf16"]
     assert max_err(got_lse, ref_lse) <= 4e-3 + 1e-5 * np.abs(ref_lse).max()
+
+
+# Pairs of k planes walk a five-slot ring (a first pair, a loop of five, a tail): pair counts
+# around its edges, on 128-wide tiles (384 features x 300 tokens) and, below, on 256-wide ones.
+@pytest.mark.parametrize("pairs", [1, 2, 3, 6, 7, 8, 9, 12, 13])
+def test_projection_k_edges(pairs):
+    B, N, Dm, H, d = 1, 300, 64 * pairs, 2, 64
+    x, ws = _inputs(B, N, Dm, H, d, _seed("k", pairs))
+    _, _, qkv = _run(x, ws, H, False)
+    for got, want, w in zip(qkv, oracle.attention_proj(x, *ws, H, d)[1:4], ws):
+        assert _check_projection(got, want, x, w, H, d) < 0.01
+
+
+@pytest.mark.parametrize("pairs", [1, 2, 5, 8])
+def test_projection_wide_tiles(pairs):
+    # 16 x 15 tiles of 256: the rule takes the large tile; checked against fp32 products.
+    import torch
+    import paper_2606_07713_amd as moa
+    B, N, Dm, H, d = 2, 2001, 64 * pairs, 20, 64
+    g = torch.Generator(device="cuda").manual_seed(pairs)
+    x = torch.randn((B, N, Dm), device="cuda", generator=g).bfloat16()
+    ws = [(torch.randn((H * d, Dm), device="cuda", generator=g) * Dm ** -0.5).bfloat16() for _ in range(3)]
+    _, qkv = moa.attn_fwd_proj(x, *ws, H, return_qkv=True)
+    for got, w in zip(qkv, ws):
+        want = (x.double().view(-1, Dm) @ w.double().t().contiguous()).view(B, N, H, d).transpose(1, 2)
+        absum = (x.double().abs().view(-1, Dm) @ w.double().abs().t().contiguous()).view(B, N, H, d).transpose(1, 2)
+        err = (got.double() - want).abs()
+        assert bool((err <= want.abs() * 2.0 ** -7 + Dm * 2.0 ** -23 * absum).all())
