@@ -62,7 +62,9 @@ hipError_t launch_prefill_gather(const Problem& p, const GatherLayout& g, hipStr
 
 // Prefill, bf16 inputs: one launch of the MFMA tile kernel.
 hipError_t launch_prefill_bf16(const Problem& p, hipStream_t stream);
-
+// The same on small independent workgroups (chosen by launch_prefill_bf16);
+// `cus` = compute units of the device.
+hipError_t launch_prefill_indep(const Problem& p, int cus, hipStream_t stream);
 
 // Prefill, fp32 inputs: one launch of the fp32 vector-ALU kernel (smallest
 // grids) or of the fp32 matrix-core kernel.
@@ -115,6 +117,8 @@ hipError_t noalloc_scratch(hipStream_t stream, void** ptr);
 
 // Row-tile size of the bf16 prefill kernel (queries per workgroup).
 constexpr int kPrefillBf16RowsPerBlock = 256;
+// Of its independent-workgroup kernel.
+constexpr int kPrefillIndepRowsPerBlock = 128;
 // Row-tile size of the fp32 prefill kernel.
 constexpr int kPrefillF32RowsPerBlock = 16;
 // Row-tile size of the element-gather kernel.

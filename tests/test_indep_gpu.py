@@ -1,0 +1,75 @@
+"""The independent-workgroup bf16 prefill (grids of uneven rounds) against the fp64 oracle on
+sampled rows; the launch rule sends every shape here to it on a 256-unit GPU.  Tolerances as
+everywhere: 2e-2 for O, 4e-3 (bf16 weights) plus fp32 rounding for LSE."""
+import zlib
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import TOL, gen, max_err, run_gpu, sample_rows, say
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # B, H, Nq, Nk: rows and keys on both sides of a wave (32), a tile (64), an item (128)
+    (1, 300, 2, 3), (2, 150, 33, 65), (1, 290, 128, 128), (4, 50, 200, 200), (3, 80, 255, 320),
+    (2, 65, 257, 511),
+]
+
+
+def _check(q, k, v, o, lse, causal, scale=None):
+    B, H, Nq, d = o.shape
+    rows = sample_rows(B, H, Nq, 300, seed=5)
+    ref, ref_lse = oracle.attention_rows(q, k, v, rows, scale=scale, causal=causal, with_lse=True)
+    err = max_err(o.reshape(-1, d)[rows], ref)
+    say(f"  max err {err:.3e}")
+    assert err <= TOL["bf16"]
+    assert max_err(lse.reshape(-1)[rows], ref_lse) <= 4e-3 + 1e-5 * np.abs(ref_lse).max()
+    assert np.isfinite(o).all() and np.isfinite(lse).all()
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("out_dtype", ["bf16", "f32"])
+def test_independent_workgroups_match_oracle(shape, d, causal, out_dtype):
+    B, H, Nq, Nk = shape
+    q, k, v = gen(B, H, Nq, Nk, d, "bf16", seed=zlib.crc32(repr((shape, d, causal)).encode()) % 9973)
+    o, lse = run_gpu(q, k, v, causal=causal, out_dtype=out_dtype, return_lse=True)
+    _check(q, k, v, o, lse, causal)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale", [-0.3, 4.0, 0.0])
+def test_independent_workgroups_scales(d, scale):
+    # A negative scale, wide logits (the reference is raised over and over) and uniform weights.
+    q, k, v = gen(2, 100, 150, 300, d, "bf16", seed=31)
+    o, lse = run_gpu(q, k, v, causal=True, scale=scale, out_dtype="f32", return_lse=True)
+    _check(q, k, v, o, lse, True, scale)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+def test_independent_workgroups_packed_layout(d, causal):
+    # [B][N][3][H][d] projections in, O in [B][N][H][d]: bit-identical to the contiguous call.
+    import torch
+    import paper_2606_07713_amd as moa
+    B, N, H = 6, 230, 30
+    qkv = torch.randn((B, N, 3, H, d), device="cuda").bfloat16()
+    q, k, v = (qkv[:, :, i].transpose(1, 2) for i in range(3))
+    out = torch.empty((B, N, H, d), dtype=torch.bfloat16, device="cuda").transpose(1, 2)
+    moa.attn_fwd(q, k, v, causal=causal, out=out)
+    ref = moa.attn_fwd(*(t.contiguous() for t in (q, k, v)), causal=causal)
+    assert torch.equal(out, ref)
+
+
+def test_more_items_than_resident_workgroups():
+    # Several items per workgroup, the last layer of items partly empty.
+    q, k, v = gen(1, 700, 200, 190, 64, "bf16", seed=77)
+    o, lse = run_gpu(q, k, v, out_dtype="f32", return_lse=True)
+    _check(q, k, v, o, lse, False)
+    q, k, v = gen(1, 700, 190, 200, 128, "bf16", seed=78)
+    o, lse = run_gpu(q, k, v, causal=True, out_dtype="f32", return_lse=True)
+    _check(q, k, v, o, lse, True)
