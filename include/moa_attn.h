@@ -79,8 +79,8 @@ enum {
  * (Nq > 1) split when the library's choice (or `num_splits` > 1) says so:
  * automatically only for grids too small to fill the GPU (fewer than 128
  * tiles of 256 queries over all B*H slices, and at least 2048 keys), where
- * splits * (128-query tiles) approaches 256 workgroups with at least 1024
- * keys per split.  fp32 prefill never splits (its call ignores the
+ * splits * (128- or 256-query tiles) comes near one or two rounds of 256
+ * workgroups with at least 1024 keys per split.  fp32 prefill never splits (its call ignores the
  * workspace).  Returns 0 when the call does not split and for invalid
  * dimensions.
  */
@@ -121,7 +121,8 @@ int moa_attn_num_splits(int64_t B, int64_t H, int64_t Nq, int64_t Nk, int64_t dk
  *           split and for bf16 prefill with num_splits > 1 (else
  *           MOA_ERR_WORKSPACE);
  *           a bf16 prefill call with num_splits == 0 whose workspace is
- *           missing or too small runs in one pass instead.  May be NULL/0
+ *           missing or too small for the library's choice splits less, in
+ *           the end not at all.  May be NULL/0
  *           when moa_attn_workspace_bytes(...) is 0.
  * num_splits
  *           key splits across workgroups (0 = library's choice, else

@@ -22,8 +22,8 @@ constexpr int64_t kMinKeysPerSplit = 256;
 constexpr int64_t kTargetDecodeBlocks = 256;
 // Prefill (Nq > 1, bf16): keys are split across workgroups when fewer than
 // kPrefillSplitBelowItems 256-query items exist (half the 256 compute units
-// of an MI355X), aiming at kPrefillTargetBlocks 128-query split items, each
-// split covering at least kMinKeysPerPrefillSplit keys.
+// of an MI355X), aiming at kPrefillTargetBlocks split items, each split
+// covering at least kMinKeysPerPrefillSplit keys (see prefill_split_choices).
 constexpr int64_t kPrefillSplitBelowItems = 128;
 constexpr int64_t kPrefillTargetBlocks = 256;
 constexpr int64_t kMinKeysPerPrefillSplit = 1024;
@@ -58,26 +58,78 @@ int pick_splits(int64_t bh, int64_t Nk, int requested) {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-int pick_prefill_splits(int64_t bh, int64_t Nq, int64_t Nk, int requested) {
-    if (requested > 0) return requested;
-    if (bh * ((Nq + 255) / 256) >= kPrefillSplitBelowItems) return 1;
+size_t prefill_ws_bytes(int64_t bh, int64_t Nq, int64_t d, int splits) {
+    return align256((size_t)bh * (size_t)Nq * (size_t)splits * (size_t)(d + 2) * sizeof(float));
+}
+
+// How an automatic split-K prefill may run, best first; a call takes the first
+// one whose partial states fit its workspace, or one pass.  `wide`: 256-query
+// items (one key stream each) instead of 128-query items (two streams that
+// meet in the workgroup, so half the partial states for the same number of
+// workgroups).
+struct SplitChoice {
+    int splits;
+    bool wide;
+};
+struct SplitChoices {
+    SplitChoice c[3];
+    int n = 0;
+};
+
+// Narrow items: the splits whose items make one round of the compute units, or
+// two when those halve the keys per round well enough (the old rule rounded
+// up and could leave a second round nearly empty: B2 H20 100 x 8000 d = 128, 7
+// splits 53.2 us, 6 splits 36.2).  Wide items stream faster (one K/V tile
+// serves 256 queries and the two halves of the workgroup alternate matrix and
+// vector phases) but write twice the states: where there are queries for
+// both halves, at least two wide splits to a narrow one, and keys enough
+// (2048 per split at d = 64): B1 H32 200 x 20011 d = 128 108.8 -> 97.8 us, d =
+// 64 60.2 -> 58.2; B2 H8 700 x 9000 d = 128 83.9 -> 72.4; too short, B1 H12
+// 300 x 6000 d = 64: 21.6 narrow, 25.5 wide.  Choices beyond the first stay
+// within the fixed scratch array, so that a call with it and one with the
+// queried workspace take the same.
+SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d) {
+    SplitChoices r;
+    const int64_t wide_items = bh * ((Nq + 255) / 256), items = bh * ((Nq + 127) / 128);
+    if (wide_items >= kPrefillSplitBelowItems) return r;
+    int64_t cap = Nk / kMinKeysPerPrefillSplit;
+    if (cap > kMaxSplits) cap = kMaxSplits;
+    const auto capped = [&](int64_t s) { return s > cap ? cap : s; };
+    const int64_t s1 = capped(kPrefillTargetBlocks / items), s2 = capped(2 * kPrefillTargetBlocks / items);
+    const int64_t sw = kPrefillTargetBlocks / wide_items;
+    const auto fits = [&](int64_t s) { return prefill_ws_bytes(bh, Nq, d, (int)s) <= moa::kNoallocScratchBytes; };
+    const int64_t wide_cap = d == 64 ? cap / 2 : cap;
+    if (Nq > 128 && sw <= wide_cap && sw >= 2 * s1 && sw >= s2 && sw > 1 && fits(sw))
+        r.c[r.n++] = {(int)sw, true};
+    if (200 * s1 < 85 * s2 && s2 > 1 && fits(s2)) r.c[r.n++] = {(int)s2, false};
+    if (s1 > 1) r.c[r.n++] = {(int)s1, false};
+    else if (r.n && r.c[0].wide && sw > 2) r.c[r.n++] = {2, true};
+    return r;
+}
+
+// Partial states of a call that splits its keys as often as its 128-query
+// items, rounded up, go into the target: what a workspace had to hold before
+// the choices above, and still suffices for one of them.
+size_t prefill_least_ws_bytes(int64_t bh, int64_t Nq, int64_t Nk, int64_t d) {
+    if (bh * ((Nq + 255) / 256) >= kPrefillSplitBelowItems) return 0;
     const int64_t items = bh * ((Nq + 127) / 128);
     int64_t s = (kPrefillTargetBlocks + items - 1) / items;
     const int64_t cap = Nk / kMinKeysPerPrefillSplit;
     if (s > cap) s = cap;
     if (s > kMaxSplits) s = kMaxSplits;
-    if (s < 1) s = 1;
-    return (int)s;
+    return s > 1 ? prefill_ws_bytes(bh, Nq, d, (int)s) : 0;
+}
+
+int pick_prefill_splits(int64_t bh, int64_t Nq, int64_t Nk, int64_t d, int requested) {
+    if (requested > 0) return requested;
+    const SplitChoices r = prefill_split_choices(bh, Nq, Nk, d);
+    return r.n ? r.c[0].splits : 1;
 }
 
 // Split-K work items (128-query tiles x splits per head slice) must fit the
 // kernels' 32-bit counters.
 bool prefill_splits_fit(int64_t bh, int64_t Nq, int splits) {
     return bh * ((Nq + 127) / 128) * splits <= std::numeric_limits<int32_t>::max();
-}
-
-size_t prefill_ws_bytes(int64_t bh, int64_t Nq, int64_t d, int splits) {
-    return align256((size_t)bh * (size_t)Nq * (size_t)splits * (size_t)(d + 2) * sizeof(float));
 }
 
 // Name of the HIP error behind the last MOA_ERR_HIP returned on this thread.
@@ -182,7 +234,7 @@ int moa_attn_num_splits(int64_t B, int64_t H, int64_t Nq, int64_t Nk, int64_t dk
     if (num_splits < 0 || num_splits > kMaxSplits) return 1;
     if (Nq == 1) return pick_splits(B * H, Nk, num_splits);
     if (B * H == 0) return 1;
-    return pick_prefill_splits(B * H, Nq, Nk, num_splits);
+    return pick_prefill_splits(B * H, Nq, Nk, dk, num_splits);
 }
 
 size_t moa_attn_workspace_bytes(int64_t B, int64_t H, int64_t Nq, int64_t Nk, int64_t dk,
@@ -193,7 +245,7 @@ size_t moa_attn_workspace_bytes(int64_t B, int64_t H, int64_t Nq, int64_t Nk, in
     const int64_t bh = B * H;
     if (bh == 0) return 0;
     if (Nq == 1) return decode_ws_bytes(bh, dk, pick_splits(bh, Nk, num_splits));
-    const int s = pick_prefill_splits(bh, Nq, Nk, num_splits);
+    const int s = pick_prefill_splits(bh, Nq, Nk, dk, num_splits);
     if (s <= 1 || !prefill_splits_fit(bh, Nq, s)) return 0;
     return prefill_ws_bytes(bh, Nq, dk, s);
 }
@@ -261,6 +313,7 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, i
 
     const bool decode = (Nq == 1);
     int splits = 1;
+    bool wide = false;
     size_t need = 0;
     if (decode && bh > 0) {
         splits = pick_splits(bh, Nk, num_splits);
@@ -268,14 +321,22 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, i
         if (need && !ws_fits(need)) return short_ws;
     } else if (!decode && bh > 0 && Nq > 0 && in_dtype == MOA_BF16) {
         // Split-K prefill: explicitly requested splits need the workspace;
-        // the automatic choice falls back to one pass without it.
-        splits = pick_prefill_splits(bh, Nq, Nk, num_splits);
-        if (splits > 1 && !prefill_splits_fit(bh, Nq, splits)) return MOA_ERR_UNSUPPORTED;
-        need = splits > 1 ? prefill_ws_bytes(bh, Nq, dk, splits) : 0;
-        if (need && !ws_fits(need)) {
-            if (num_splits > 1) return short_ws;
-            splits = 1;
-            need = 0;
+        // the automatic choice takes what fits, in the end one pass.
+        const SplitChoices ch = prefill_split_choices(bh, Nq, Nk, dk);
+        if (num_splits > 0) {
+            splits = num_splits;
+            wide = ch.n > 0 && ch.c[0].wide && ch.c[0].splits == splits;
+            if (splits > 1 && !prefill_splits_fit(bh, Nq, splits)) return MOA_ERR_UNSUPPORTED;
+            need = splits > 1 ? prefill_ws_bytes(bh, Nq, dk, splits) : 0;
+            if (need && !ws_fits(need)) return short_ws;
+        }
+        for (int i = 0; num_splits == 0 && i < ch.n; ++i) {
+            const size_t n = prefill_ws_bytes(bh, Nq, dk, ch.c[i].splits);
+            if (!ws_fits(n)) continue;
+            splits = ch.c[i].splits;
+            wide = ch.c[i].wide;
+            need = n;
+            break;
         }
     }
     if (need && !use_scratch) {
@@ -307,6 +368,7 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, i
     p.lay.ob = so.b; p.lay.oh = so.h; p.lay.orow = (int)so.r;
     p.lay.H = (int)H;
     p.splits = splits;
+    p.split_wide = wide;
     p.ws = static_cast<float*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
 
@@ -537,7 +599,11 @@ int moa_attn_fwd_proj(const void* X, const void* Wq, const void* Wk, const void*
     if (tokens > lim || H * d > lim / 3 || (tokens > 0 && Dm > lim / tokens)) return MOA_ERR_UNSUPPORTED;
     if (!any) return MOA_OK;
 
-    const size_t need = moa_attn_proj_workspace_bytes(B, N, Dm, H, d);
+    // The queried size, or as little as one of the attention's choices needs.
+    const size_t qkv = align256((size_t)(bh * N * d) * 2);
+    size_t need = moa_attn_proj_workspace_bytes(B, N, Dm, H, d);
+    if (N > 1 && workspace_bytes < need && workspace_bytes >= 3 * qkv + prefill_least_ws_bytes(bh, N, N, d))
+        need = workspace_bytes;
     if (!workspace || workspace_bytes < need) return MOA_ERR_WORKSPACE;
     const size_t xn = (size_t)(tokens * Dm) * 2, wn = (size_t)(H * d * Dm) * 2;
     const size_t on = (size_t)(bh * N * d) * (out_dtype == MOA_F32 ? 4 : 2);
@@ -553,7 +619,6 @@ int moa_attn_fwd_proj(const void* X, const void* Wq, const void* Wk, const void*
     }
 
     // Q, K, V (bf16, [B][H][N][d]) and the attention's own workspace.
-    const size_t qkv = align256((size_t)(bh * N * d) * 2);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     moa::ProjProblem pp;
     pp.x = X;

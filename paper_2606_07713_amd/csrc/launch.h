@@ -35,6 +35,7 @@ struct Problem {
     // Key splits of a split-K launch (1 = none) and its fp32 workspace:
     // partial states [bh * nq][splits][d] followed by [bh * nq][splits][2].
     int splits;
+    bool split_wide;   // split prefill: 256-query items (else 128-query items)
     float* ws;
 };
 

@@ -68,8 +68,8 @@ __device__ __forceinline__ void wait_loads_to_lds() {
 //   groups in the same phase), and group 1 hands its softmax state (m, l, O)
 //   to group 0 through LDS at the end for an exact merge.  Used for grids
 //   the ping-pong layout would leave partly idle (see use_key_split).
-// PARTIAL = true (with KSPLIT): split-K across workgroups for grids smaller
-//   still.  Work item = (batch*head, query tile, key split s of n_splits):
+// PARTIAL = true: split-K across workgroups for grids smaller still, on either
+//   layout.  Work item = (batch*head, query tile, key split s of n_splits):
 //   the item covers the s-th of n_splits equal shares of the query tile's
 //   visible key tiles and, instead of O, writes its partial state -- the
 //   reference m (log2 units), the denominator l and the un-normalised output
@@ -81,7 +81,6 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     const u16* __restrict__ Q, const u16* __restrict__ K, const u16* __restrict__ V,
     void* __restrict__ Out, float* __restrict__ LSE, int Nq, int Nk, int n_bh, int n_qtiles, float c,
     Layout L, int n_splits) {
-    static_assert(!PARTIAL || KSPLIT, "split-K items use the key-split layout");
     const Addr<D, STRIDED> A{L, Nq, Nk};
     using C = Cfg<D>;
     constexpr uint32_t RB = C::ROW_BYTES;
@@ -220,7 +219,9 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     const int wave_q_first = q0 + qw * 32;
     int w_end = n_kt;                                         // global tiles this wave needs
     if (CAUSAL) w_end = min(n_kt, (wave_q_first + 31 + off) / BN + 1);
-    const int n_w = max(0, min(g_start + g_count, w_end) - g_start);   // local count
+    int n_w = max(0, min(g_start + g_count, w_end) - g_start);   // local count
+    // A split item's waves without queries leave the SIMD to their partners.
+    if (PARTIAL && !KSPLIT && wave_q_first >= Nq) n_w = 0;
 
     // ---- a2: direct-to-LDS tile loads.  Lane l of the i-th load of loader lw
     // fills slot S = (lw*LPW + i)*64 + l of its stream's tile, which holds
@@ -553,7 +554,7 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     // ---- a8 (split-K): the partial state of this key share, un-normalised,
     // for the combine pass.
     if constexpr (PARTIAL) {
-    if (grp == 0) {
+    if (!KSPLIT || grp == 0) {
         const float l_tot = half_sum(l_run);
         store_rows_f32(1.0f, [&](int r) -> float* {
             const int q = wave_q_first + r;
@@ -717,8 +718,11 @@ hipError_t launch(const Problem& p, hipStream_t stream) {
         // Split-K: partial states of every key share, then the exact merge.
         float* ws_acc = p.ws;
         float* ws_ml = p.ws + (size_t)p.bh * p.nq * p.splits * D;
-        const hipError_t e = launch_persistent<D, CAUSAL, false, true, STRIDED, true>(
-            p, qt_ks * p.splits, c, ws_acc, ws_ml, p.splits, stream);
+        const hipError_t e =
+            p.split_wide ? launch_persistent<D, CAUSAL, false, false, STRIDED, true>(
+                               p, qt_pp * p.splits, c, ws_acc, ws_ml, p.splits, stream)
+                         : launch_persistent<D, CAUSAL, false, true, STRIDED, true>(
+                               p, qt_ks * p.splits, c, ws_acc, ws_ml, p.splits, stream);
         if (e != hipSuccess) return e;
         return launch_split_combine(p, p.splits, ws_acc, ws_ml, stream);
     }

@@ -356,3 +356,44 @@ def test_onf_validation():
                      k_strides=colmajor(4, 300, 64)) == moa.MOA_ERR_INVALID_ARG
     # LSE must not overlap O either
     assert _call_onf(LSE=(4 << 40) + 256, k_strides=colmajor(4, 300, 64)) == moa.MOA_ERR_INVALID_ARG
+
+
+def test_prefill_split_choices_are_consistent():
+    # The workspace query matches the split count, automatic choices fit the fixed scratch array
+    # where narrower ones did, and a split never leaves the target of 256 items per round short
+    # of one round by rounding up.
+    for bh in (1, 2, 3, 8, 12, 16, 32, 40, 60, 100, 127):
+        for nq in (2, 64, 100, 128, 129, 200, 256, 300, 700, 1024, 4096):
+            for nk in (nq, 1500, 2048, 5000, 9000, 20011, 65536):
+                for d in (64, 128):
+                    if nk < nq:
+                        continue
+                    s = moa.moa_attn_num_splits(1, bh, nq, nk, d, d, 0)
+                    ws = moa.moa_attn_workspace_bytes(1, bh, nq, nk, d, d, 0)
+                    assert 1 <= s <= max(1, nk // 1024)
+                    assert ws == (0 if s == 1 else -(-bh * nq * s * (d + 2) * 4 // 256) * 256)
+                    if bh * -(-nq // 256) >= 128:
+                        assert s == 1
+                    assert s == 1 or bh * -(-nq // 256) * s <= 512
+                    # at least the splits of the old rule rounded down, and no more states than
+                    # the scratch array unless that rule needed them too
+                    items = bh * -(-nq // 128)
+                    if bh * -(-nq // 256) < 128:
+                        assert s >= min(256 // items, nk // 1024)
+                    assert ws <= moa.MOA_NOALLOC_SCRATCH_BYTES or s <= 256 // items
+
+
+def test_proj_takes_the_workspaces_it_took():
+    # A workspace sized for the splits of 128-query items, rounded up, is still accepted: the
+    # call gets past the workspace check (to the overlap check, made to fail).
+    W0 = 1 << 44
+    for B, N, H, d in ((1, 8192, 2, 64), (1, 4096, 4, 64), (2, 2048, 4, 128), (1, 8192, 2, 128)):
+        qkv = -(-B * H * N * d * 2 // 256) * 256
+        items = B * H * -(-N // 128)
+        s = min(-(-256 // items), N // 1024)
+        old = 3 * qkv + (-(-B * H * N * s * (d + 2) * 4 // 256) * 256 if s > 1 else 0)
+        need = moa.moa_attn_proj_workspace_bytes(B, N, 64, H, d)
+        for size in {old, need, min(old, need) - 256}:
+            st = moa.moa_attn_fwd_proj(W0, 2 << 44, 3 << 44, 4 << 44, W0, None, B, N, 64, H, d, 0.1, 0,
+                                       moa.MOA_BF16, 5 << 44, size, None)
+            assert st == (moa.MOA_ERR_INVALID_ARG if size >= min(old, need) else moa.MOA_ERR_WORKSPACE)

@@ -135,3 +135,41 @@ def test_combine_keeps_infinities():
     o = moa.attn_fwd(q, k, v, num_splits=5)
     assert torch.isposinf(o[..., 5]).all()
     assert torch.isfinite(o[..., :5]).all() and torch.isfinite(o[..., 6:]).all()
+
+
+WIDE = [
+    # B, H, Nq, Nk, d: 256-query split items (two to a narrow one); ragged rows and keys
+    (2, 30, 130, 4100, 128),
+    (1, 32, 200, 8200, 128),
+    (1, 16, 257, 8200, 64),
+]
+
+
+@pytest.mark.parametrize("case", WIDE, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+def test_wide_splits_and_smaller_workspaces(case, causal):
+    # The automatic choice, then the same call with workspaces too small for it: fewer splits,
+    # in the end one pass, each against the oracle on sampled rows.
+    import torch
+    import oracle
+    import synth
+    from gpu_util import sample_rows
+    B, H, Nq, Nk, d = case
+    q, k, v = gen(B, H, Nq, Nk, d, "bf16", seed=_seed("wide", case, causal))
+    rows = sample_rows(B, H, Nq, 200, seed=3)
+    ref, ref_lse = oracle.attention_rows(q, k, v, rows, causal=causal, with_lse=True)
+    tq, tk, tv = (synth.to_torch(a, "cuda") for a in (q, k, v))
+    full = moa.moa_attn_workspace_bytes(B, H, Nq, Nk, d, d)
+    splits = moa.moa_attn_num_splits(B, H, Nq, Nk, d, d)
+    assert splits >= 4 and full >= B * H * Nq * splits * (d + 2) * 4
+    for size in (full, full - 256, full // 2, 256):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        o, lse = moa.attn_fwd(tq, tk, tv, causal=causal, out_dtype=torch.float32, return_lse=True,
+                              workspace=ws)
+        err = max_err(o.cpu().double().numpy().reshape(-1, d)[rows], ref)
+        say(f"wide {case} causal={causal} workspace {size}: max err {err:.3e}")
+        assert err <= TOL["bf16"]
+        assert max_err(lse.cpu().double().numpy().reshape(-1)[rows], ref_lse) <= _lse_tol(ref_lse)
+    # Asked for explicitly, the automatic split count is the automatic choice.
+    a = moa.attn_fwd(tq, tk, tv, causal=causal)
+    assert torch.equal(a, moa.attn_fwd(tq, tk, tv, causal=causal, num_splits=splits))
