@@ -648,7 +648,7 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 }
 
 // Small independent workgroups (prefill_bf16_indep.hip) take 128 queries at a
-// time without splitting the keys, two to four workgroups to a compute unit.
+// time without splitting the keys, two or three workgroups to a compute unit.
 // A compute unit's 128-query load W (items per unit, rounded up) costs about
 // 0.52 W (d = 64) or 0.6 W (d = 128) of a ping-pong round r, the empty part of
 // a ragged last tile nothing.  Measured, us, one head per batch entry, today's
@@ -658,28 +658,28 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 //     120 x 300 d 64 14.5 / 11.7, d 128 21.0 / 16.7; 40 x 1100 28.8 / 27.0, 43.8 / 39.5;
 //     45 x 1100 29.7 / 30.5, 50.3 / 42.8
 //   unmasked, more: W, r
-//     d 64:  69 x 777 [2, 2] 37.1 / 25.1; 106 x 777 [3, 2] 38.0 / 32.1; 73 x 1500 [4, 2]
-//            61.1 / 65.2; 102 x 1500 [5, 3] 91.4 / 78.5; 119 x 1500 [6, 3] 95.8 / 96.4
+//     d 64:  69 x 777 [2, 2] 37.8 / 21.8; 96 x 777 [3, 2] 37.5 / 28.2; 73 x 1500 [4, 2]
+//            61.1 / 65.2; 102 x 1500 [5, 3] 94.1 / 78.8; 119 x 1500 [6, 3] 95.8 / 96.4
 //     d 128: 69 x 777 [2, 2] 53.9 / 38.0; 143 x 777 [4, 3] 83.3 / 72.0; 124 x 777 [4, 2]
 //            58.9 / 64.9; 102 x 1500 [5, 3] 145 / 148; where the key split applies it is
 //            ahead from 3000 keys on (26 x 3000 [3, 2] 150 / 161)
 //   causal (the ping-pong's 256-query items also compute more of the masked corner):
-//     d 64:  290 x 300 30.1 / 17.8; 176 x 777 47.3 / 29.0; 51 x 3000 90.8 / 76.9; 32 x 4096
-//            91.0 / 84.5; 32 x 8192 322 / 311; 8 x 16384 304 / 318
+//     d 64:  290 x 300 30.0 / 17.8; 176 x 777 48.2 / 29.3; 51 x 3000 93.8 / 77.0; 32 x 4096
+//            88.9 / 82.7; 32 x 8192 326 / 303; 8 x 16384 304 / 318
 //     d 128: 290 x 300 41.2 / 28.2; 176 x 777 67.1 / 54.1; 96 x 1024 43.4 / 46.1; 51 x 3000
 //            138 / 157; exactly one item per unit, where the longest sets the time:
-//            16 x 4096 109 / 96, 8 x 8192 208 / 184
+//            16 x 4096 109 / 96, 8 x 8192 208 / 184 (not with strided rows: 110 / 113)
 //     key-split grids (fewer 256-query items than units): 127 x 512 d 64 16.9 / 15.1, d 128
 //            26.3 / 22.8; 45 x 777 15.4 / 17.4, 22.7 / 24.0
 // A mask that hides less than a quarter of the scores is treated as none
 // (80 x 700 of 2000: 46.2 / 39.2, 70.4 / 62.8).
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, bool STRIDED>
 bool use_indep(long long items256, long long items128, int nq, int nk, int cus) {
     if (items128 <= cus) return false;
     const long long W = (items128 + cus - 1) / cus, r = (items256 + cus - 1) / cus;
     if (CAUSAL && 2LL * nq > nk) {
         if (items256 < cus) return nk <= 512;
-        return D == 64 ? nk <= 8192 : (nk <= 896 || r == 1);
+        return D == 64 ? nk <= 8192 : (nk <= 896 || (r == 1 && !STRIDED));
     }
     if (items256 < cus) return D == 128 || nk < 1024 || 2 * items128 <= 3 * cus;
     if (D == 64) return 13 * W < 25 * r;
@@ -729,7 +729,7 @@ hipError_t launch(const Problem& p, hipStream_t stream) {
     int cus = 0;
     const hipError_t e = device_cus(stream, cus);
     if (e != hipSuccess) return e;
-    if (use_indep<D, CAUSAL>((long long)p.bh * qt_pp, (long long)p.bh * qt_ks, p.nq, p.nk, cus))
+    if (use_indep<D, CAUSAL, STRIDED>((long long)p.bh * qt_pp, (long long)p.bh * qt_ks, p.nq, p.nk, cus))
         return launch_prefill_indep(p, cus, stream);
     if (p.nk > BN &&
         use_key_split<CAUSAL>((long long)p.bh * qt_pp, (long long)p.bh * qt_ks, p.nk, cus))

@@ -1,7 +1,7 @@
 // bf16 prefill with small independent workgroups, for grids that the layouts
 // of prefill_bf16.hip would run in uneven rounds (see use_indep there).
 //
-// One workgroup = 4 waves x 32 queries of one (b, h), one wave per SIMD; four
+// One workgroup = 4 waves x 32 queries of one (b, h), one wave per SIMD; three
 // workgroups (d = 64) or two (d = 128) share a compute unit.  K and V stream
 // through a two-stage LDS ring in 64-key tiles, one barrier per tile, and each
 // wave takes its 32-key steps one after the other: S^T = K Q^T, the softmax of
@@ -9,15 +9,18 @@
 // that share a SIMD; the other workgroups fill the gaps of each.
 //
 // What bounds it is the sum of a SIMD's matrix and vector work, as in the
-// ping-pong layout, and at full grids it only matches that one (B4 H16 2K d =
-// 64: 85.9 against 87.9 us).  Its gain is the grain: a compute unit takes 128
-// queries at a time instead of 256, so grids of one and a half rounds do not
-// pay for two, and a wave without queries costs nothing.  B8 H12 777 d = 64:
-// 39.1 -> 31.1 us (380 -> 477 TFLOP/s), B8 H12 777 d = 128: 57.5 -> 52.5.
+// ping-pong layout, and at full grids it only matches that one (32 x 4096 d =
+// 64: 150 us both).  Its gain is the grain: a compute unit takes 128 queries at
+// a time instead of 256, so grids of one and a half rounds do not pay for two,
+// causal items reach less far past the diagonal, and a wave without queries
+// costs nothing.  B8 H12 777 d = 64: 39.1 -> 28.2 us (380 -> 527 TFLOP/s),
+// causal in the packed layout 31.2 -> 18.9; d = 128: 57.5 -> 52.5.
 //
-// Registers: at d = 64 four waves per SIMD leave 128, which is why S and P are
-// held for 32 keys at a time (64 at a time spilled 77).  At d = 128 the same
-// with three waves per SIMD spilled in the loop (four times slower).
+// Registers: S and P are held for 32 keys at a time, which leaves 136 at d = 64,
+// three waves per SIMD without a spill.  Four waves (128 registers, 6 to 12
+// spilled in the loop) were slower on every grid: 176 x 777 45.0 against 43.5
+// us, 102 x 1500 causal 50.4 / 45.2, packed B4 H12 3000 causal 95.3 / 71.8.  At d =
+// 128 three waves spilled heavily (four times slower).
 #include <algorithm>
 #include <type_traits>
 
@@ -33,7 +36,7 @@ using namespace pf;
 constexpr int IW = kPrefillIndepRowsPerBlock / 32;   // waves per workgroup
 
 template <int D, bool CAUSAL, bool OUT_BF16, bool STRIDED>
-__global__ __launch_bounds__(IW * 64, (D == 64 ? 4 : 2)) void prefill_indep_kernel(
+__global__ __launch_bounds__(IW * 64, (D == 64 ? 3 : 2)) void prefill_indep_kernel(
     const u16* __restrict__ Q, const u16* __restrict__ K, const u16* __restrict__ V,
     void* __restrict__ Out, float* __restrict__ LSE, int Nq, int Nk, int n_bh, int n_qtiles, float c,
     Layout L, int units) {
