@@ -142,20 +142,24 @@ __global__ __launch_bounds__(IW * 64, (D == 64 ? 3 : 2)) void prefill_indep_kern
             const bool need_mask = (kbase + BN > Nk) || (CAUSAL && kbase + BN - 1 > wq + off);
 #pragma unroll
             for (int sb = 0; sb < BN / SN; ++sb) {
-                f32x16 sacc = f32x16{};
+                // S^T of the tile's 32-key step u, masked.
+                auto scores = [&](int u) __attribute__((always_inline)) {
+                    f32x16 x = f32x16{};
 #pragma unroll
-                for (int s = 0; s < D / 16; ++s)
-                    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        *reinterpret_cast<const bf16x8*>(ks + kaddr[s] + sb * SN * RB), qf[s], sacc, 0, 0, 0);
-                if (need_mask) {
+                    for (int s = 0; s < D / 16; ++s)
+                        x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            *reinterpret_cast<const bf16x8*>(ks + kaddr[s] + u * SN * RB), qf[s], x, 0, 0, 0);
+                    if (need_mask) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int key = kbase + sb * SN + (i >> 2) * 8 + half * 4 + (i & 3);
-                        if (key >= Nk || (CAUSAL && key > qrow + off)) sacc[i] = kNegInf;
+                        for (int i = 0; i < 16; ++i) {
+                            const int key = kbase + u * SN + (i >> 2) * 8 + half * 4 + (i & 3);
+                            if (key >= Nk || (CAUSAL && key > qrow + off)) x[i] = kNegInf;
+                        }
                     }
-                }
-                auto raise_reference = [&]() __attribute__((always_inline)) {
-                    float mx = kNegInf;
+                    return x;
+                };
+                f32x16 sacc = scores(sb);
+                auto raise_reference = [&](float mx) __attribute__((always_inline)) {
                     asm volatile("" : "+v"(mx));   // not hoisted onto the fast path
 #pragma unroll
                     for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[i]);
@@ -191,10 +195,22 @@ __global__ __launch_bounds__(IW * 64, (D == 64 ? 3 : 2)) void prefill_indep_kern
                     }
                     return part[0] + part[1];
                 };
-                if (wave_any(m_run == kNegInf)) raise_reference();
+                // A row's first reference comes from the whole tile, as in the
+                // other layouts: the weight of the largest score is then a power
+                // of two, exact in bf16, for as many rows (with 32 keys the error
+                // of short causal rows was 2 to 7% larger).
+                if (wave_any(m_run == kNegInf)) {
+                    float mx = kNegInf;
+                    if (sb + 1 < BN / SN) {
+                        const f32x16 next = scores(sb + 1);
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, next[i]);
+                    }
+                    raise_reference(mx);
+                }
                 float part = exp_pack();
                 if (wave_any(!(part <= kFastSumLimit))) {
-                    raise_reference();
+                    raise_reference(kNegInf);
                     part = exp_pack();
                 }
                 l_run += part;
