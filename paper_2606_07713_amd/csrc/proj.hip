@@ -202,7 +202,10 @@ __global__ __launch_bounds__(WF * WM * 64, 1) void proj_kernel(ProjArgs a) {
     // previous plane's last fragments wait in F1 (`first`: none do).  At the
     // middle barrier every wave has read plane 2j and all before it, so pair
     // j + 2 (`load`: it exists) may overwrite planes 2j - 1 and 2j; at the end
-    // every wave waits for its part of pair j + 1 (`pend`: it exists).
+    // every wave waits for its part of pair j + 1 (`pend`: it exists).  The
+    // reads of F1 are not waited for there: their plane is not overwritten
+    // before the next middle barrier, which waits, or, after the last step,
+    // the barrier before the output.
     auto step = [&](int j, auto tag, auto first, bool load, bool pend) __attribute__((always_inline)) {
         constexpr int S = decltype(tag)::value;   // slot of plane 2j
         const unsigned char* pa = slot(std::integral_constant<int, S>{});
@@ -264,10 +267,14 @@ __global__ __launch_bounds__(WF * WM * 64, 1) void proj_kernel(ProjArgs a) {
     tail(integral_constant<int, 8>{});
     tail(integral_constant<int, 0>{});
     tail(integral_constant<int, 2>{});
+    // The last step's closing barrier was passed with the reads of F1 still
+    // out: once every wave has them, the ring is idle.
+    wait_lgkmcnt0();
+    barrier_no_fence();
     mul(F1);
 
-    // Output through LDS (the ring is idle): token rows of FB * 32 features,
-    // then whole rows, 16 bytes per lane.
+    // Output through LDS (the idle ring): token rows of FB * 32 features, then
+    // whole rows, 16 bytes per lane.
     constexpr int OB = FB * 64;               // bytes of a staged row
     constexpr int CH = OB / 16, RPI = 64 / CH;
     constexpr int AREA = MB * 32 * OB;

@@ -7,6 +7,10 @@ the compiler itself never keeps a value in M0 in those kernels, so the device
 assembly of the file is checked here: every M0 write lies inside one of the
 inline-assembly statements, and each of those statements is the set-up of one
 direct-to-LDS buffer load.
+
+The projection kernel (``proj.hip``) reuses its operand ring for the output
+rows; the wait and the barrier between the last operand reads and the first
+staged row are checked in its assembly.
 """
 import os
 import re
@@ -81,3 +85,40 @@ def test_m0_scan_sees_a_compiler_write():
                       "s_mov_b32 m0, -1", "ds_read_b32 v0, v1"])
     inside, outside, blocks = _m0_writes(text)
     assert outside == ["s_mov_b32 m0, -1"] and len(inside) == 1 and len(blocks) == 1
+
+
+def _unordered_reuse(asm_text):
+    """Kernels whose first LDS store is not separated from the LDS reads before it by a wait for
+    all of them (lgkmcnt 0) and then a barrier."""
+    bad, kernels = [], 0
+    for body in re.split(r"^(?=_Z\S+:)", asm_text, flags=re.M)[1:]:
+        code = [ln.split(";")[0].strip() for ln in body.split("s_endpgm")[0].split("\n")]
+        stores = [i for i, c in enumerate(code) if c.startswith("ds_write")]
+        reads = [i for i, c in enumerate(code) if c.startswith("ds_read") and stores and i < stores[0]]
+        if not stores or not reads:
+            continue
+        kernels += 1
+        between = code[reads[-1] + 1:stores[0]]
+        waits = [i for i, c in enumerate(between) if c.startswith("s_waitcnt") and "lgkmcnt(0)" in c]
+        if not waits or "s_barrier" not in between[waits[0]:]:
+            bad.append(code[0])
+    return kernels, bad
+
+
+@pytest.mark.skipif(not shutil.which(HIPCC) and not os.path.exists(HIPCC), reason="hipcc missing")
+def test_projection_ring_is_idle_before_the_output_rows(tmp_path):
+    out = str(tmp_path / "proj.s")
+    r = subprocess.run([HIPCC, *FLAGS, os.path.join(CSRC, "proj.hip"), "-o", out],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    kernels, bad = _unordered_reuse(open(out).read())
+    assert kernels == 3 and bad == []
+
+
+def test_ring_reuse_scan():
+    # The scan itself: a barrier passed with reads outstanding does not count.
+    head, read, store = "_Zk:", "ds_read_b128 v[0:3], v4", "ds_write_b64 v8, v[4:5]"
+    wait, bar = "s_waitcnt vmcnt(0) lgkmcnt(0)", "s_barrier"
+    for mid, n in (([wait, bar], 0), ([bar, wait], 1), ([bar], 1), ([wait, bar, wait], 0),
+                   (["s_waitcnt lgkmcnt(6)", bar], 1)):
+        assert len(_unordered_reuse("\n".join([head, read, *mid, store, "s_endpgm"]))[1]) == n
