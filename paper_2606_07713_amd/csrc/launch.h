@@ -64,8 +64,8 @@ hipError_t launch_prefill_gather(const Problem& p, const GatherLayout& g, hipStr
 // Prefill, bf16 inputs: one launch of the MFMA tile kernel.
 hipError_t launch_prefill_bf16(const Problem& p, hipStream_t stream);
 // The same on small independent workgroups (chosen by launch_prefill_bf16);
-// `cus` = compute units of the device.
-hipError_t launch_prefill_indep(const Problem& p, int cus, hipStream_t stream);
+// `cus` = compute units of the device, `renew`: two references per row.
+hipError_t launch_prefill_indep(const Problem& p, int cus, bool renew, hipStream_t stream);
 
 // Prefill, fp32 inputs: one launch of the fp32 vector-ALU kernel (smallest
 // grids) or of the fp32 matrix-core kernel.

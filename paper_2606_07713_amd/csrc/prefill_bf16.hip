@@ -729,10 +729,11 @@ hipError_t launch(const Problem& p, hipStream_t stream) {
     int cus = 0;
     const hipError_t e = device_cus(stream, cus);
     if (e != hipSuccess) return e;
-    if (use_indep<D, CAUSAL, STRIDED>((long long)p.bh * qt_pp, (long long)p.bh * qt_ks, p.nq, p.nk, cus))
-        return launch_prefill_indep(p, cus, stream);
-    if (p.nk > BN &&
-        use_key_split<CAUSAL>((long long)p.bh * qt_pp, (long long)p.bh * qt_ks, p.nk, cus))
+    const long long items_pp = (long long)p.bh * qt_pp, items_ks = (long long)p.bh * qt_ks;
+    const bool key_split = p.nk > BN && use_key_split<CAUSAL>(items_pp, items_ks, p.nk, cus);
+    if (use_indep<D, CAUSAL, STRIDED>(items_pp, items_ks, p.nq, p.nk, cus))
+        return launch_prefill_indep(p, cus, key_split, stream);
+    if (key_split)
         return launch_persistent<D, CAUSAL, OUT_BF16, true, STRIDED>(p, qt_ks, c, p.o, p.lse, 1,
                                                                      stream);
     return launch_persistent<D, CAUSAL, OUT_BF16, false, STRIDED>(p, qt_pp, c, p.o, p.lse, 1, stream);

@@ -25,6 +25,10 @@ constexpr float kRescaleSlack = 8.0f;        // log2 units a tile may exceed the
 // row max, and each raise costs a redone tile.
 constexpr float kRefHeadroom = 32.0f;
 constexpr float kFastSumLimit = 1048576.0f;  // 2^20: partial sum bound of the fast step
+// A reference taken anew in mid-stream (prefill_bf16_indep.hip) may fall at most
+// this far (log2 units) below the old one: the sums so far grow by at most 2^8,
+// and a tile whose scores lie lower has no weight to speak of.
+constexpr float kRenewDrop = 8.0f;
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s lds_v4s;

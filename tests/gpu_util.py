@@ -59,3 +59,34 @@ def sample_rows(B, H, Nq, n, seed=0, tile=128):
 
 def max_err(a, b):
     return float(np.max(np.abs(np.asarray(a, np.float64) - np.asarray(b, np.float64))))
+
+
+def bf16_weight_model(q, k, v, causal, starts, tile=128):
+    """O of one head (fp64 tensor) with the weights rounded to bf16 against a reference per key
+    range: weights 2^(s c - m) with m = 32 + the largest visible score (log2 units) of the first 64
+    keys of the range, at most 8 below the reference before.  q, k, v: fp64 [N, d] tensors;
+    starts(n_kt) lists the first 64-key tiles of the ranges of a query tile (`tile` rows) that sees
+    n_kt tiles."""
+    import math
+
+    import torch
+    Nq, Nk, off = q.shape[0], k.shape[0], k.shape[0] - q.shape[0]
+    out = torch.empty_like(q)
+    for q0 in range(0, Nq, tile):
+        rows = torch.arange(q0, min(Nq, q0 + tile), device=q.device)
+        n_kt = -(-(min(Nk, q0 + tile + off) if causal else Nk) // 64)
+        keys = torch.arange(min(Nk, 64 * n_kt), device=q.device)
+        s = (q[rows] @ k[keys].t().contiguous()) * (math.log2(math.e) / math.sqrt(q.shape[1]))
+        if causal:
+            s.masked_fill_(keys[None, :] > rows[:, None] + off, -math.inf)
+        first = [t for t in starts(n_kt) if t < n_kt] + [n_kt]
+        m = torch.empty_like(s)
+        ref = None
+        for a, b in zip(first, first[1:]):
+            new = s[:, 64 * a:64 * a + 64].amax(1) + 32
+            ref = new if ref is None else torch.maximum(new, ref - 8)
+            m[:, 64 * a:64 * b] = ref[:, None]
+        p = torch.exp2(s - m).to(torch.bfloat16).double()
+        w = p * torch.exp2(m - m.amax(1, keepdim=True))
+        out[rows] = (w @ v[keys]) / w.sum(1, keepdim=True)
+    return out

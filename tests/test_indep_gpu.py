@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 import synth
-from gpu_util import TOL, gen, max_err, run_gpu, sample_rows, say
+from gpu_util import TOL, bf16_weight_model, gen, max_err, run_gpu, sample_rows, say
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,25 @@ def test_more_items_than_resident_workgroups():
     q, k, v = gen(1, 700, 190, 200, 128, "bf16", seed=78)
     o, lse = run_gpu(q, k, v, causal=True, out_dtype="f32", return_lse=True)
     _check(q, k, v, o, lse, True)
+
+
+@pytest.mark.parametrize("shape", [(203, 183, 183, 64, False), (123, 267, 267, 128, False), (160, 150, 400, 64, False),
+                                   (123, 364, 364, 128, True), (120, 400, 450, 64, True)],
+                         ids=lambda s: "x".join(str(int(x)) for x in s))
+def test_second_reference_on_key_split_grids(shape):
+    # Fewer 256-query items than compute units: a row's weights are rounded against two
+    # references, as the key split would take them (one reference per row was up to 7.6% further
+    # from fp64).  The kernel agrees with a model of that rounding to a small part of the rounding
+    # itself (about 1.5e-3): fp32 scores near a tie may round the other way, about 1 in 2^12 with
+    # exponents of magnitude 2^5, sqrt(2^-12) of the error, and 3e-4 leaves a factor of three.
+    import torch
+    import paper_2606_07713_amd as moa
+    H, Nq, Nk, d, causal = shape
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((1, H, n, d), device="cuda", generator=g).bfloat16() for n in (Nq, Nk, Nk))
+    o = moa.attn_fwd(q, k, v, causal=causal, out_dtype=torch.float32)
+    for h in (0, H // 2, H - 1):
+        want = bf16_weight_model(*(t[0, h].double() for t in (q, k, v)), causal, lambda n: (0, (n + 1) // 2))
+        diff = float((o[0, h].double() - want).norm() / want.norm())
+        say(f"  head {h}: {diff:.2e} from the two-reference model")
+        assert diff <= 3e-4
