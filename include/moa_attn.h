@@ -90,7 +90,9 @@ size_t moa_attn_workspace_bytes(int64_t B, int64_t H, int64_t Nq, int64_t Nk, in
 /*
  * moa_attn_num_splits -- the number of key splits a call with these
  * arguments will use when given moa_attn_workspace_bytes(...) of workspace
- * (decode-shaped calls, and bf16 prefill; 1 = no split).
+ * (decode-shaped calls, and bf16 prefill; 1 = no split).  Neither query knows
+ * the mask: where the library's choice for prefill depends on it (Nk < 2 Nq),
+ * both report for the larger of the two choices.
  */
 int moa_attn_num_splits(int64_t B, int64_t H, int64_t Nq, int64_t Nk, int64_t dk, int64_t dv,
                         int num_splits);
@@ -236,8 +238,9 @@ int moa_attn_fwd_onf(const void* Q, const void* K, const void* V, void* O, float
  *  - A call whose key splits need more than MOA_NOALLOC_SCRATCH_BYTES of
  *    partial states (moa_attn_workspace_bytes(...) with the same arguments)
  *    returns MOA_ERR_SCRATCH: decode-shaped calls, and prefill calls with
- *    num_splits > 1.  With num_splits == 0 such a prefill call runs in one
- *    pass instead, exactly as moa_attn_fwd does with too small a workspace.
+ *    num_splits > 1.  With num_splits == 0 such a prefill call splits less, in
+ *    the end not at all, exactly as moa_attn_fwd does with too small a
+ *    workspace.
  *    The automatic split choice stays within the array for every problem
  *    size whose partial states need at most 32 MiB (e.g. decode with up to
  *    B*H = 8192 heads at any Nk, or any prefill whose split items fill one

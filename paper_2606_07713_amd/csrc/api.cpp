@@ -62,6 +62,16 @@ size_t prefill_ws_bytes(int64_t bh, int64_t Nq, int64_t d, int splits) {
     return align256((size_t)bh * (size_t)Nq * (size_t)splits * (size_t)(d + 2) * sizeof(float));
 }
 
+// As many splits as 128-query items go into the target, rounded up.
+int splits_rounded_up(int64_t bh, int64_t Nq, int64_t Nk) {
+    const int64_t items = bh * ((Nq + 127) / 128);
+    int64_t s = (kPrefillTargetBlocks + items - 1) / items;
+    const int64_t cap = Nk / kMinKeysPerPrefillSplit;
+    if (s > cap) s = cap;
+    if (s > kMaxSplits) s = kMaxSplits;
+    return s > 1 ? (int)s : 1;
+}
+
 // How an automatic split-K prefill may run, best first; a call takes the first
 // one whose partial states fit its workspace, or one pass.  `wide`: 256-query
 // items (one key stream each) instead of 128-query items (two streams that
@@ -88,10 +98,23 @@ struct SplitChoices {
 // 300 x 6000 d = 64: 21.6 narrow, 25.5 wide.  Choices beyond the first stay
 // within the fixed scratch array, so that a call with it and one with the
 // queried workspace take the same.
-SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d) {
+//
+// A causal mask that hides more than a quarter of the scores (`hides`) makes
+// items of unequal length, which even out only over several of them per unit:
+// as many 128-query splits as go into the target, rounded up, in the snake
+// order of item_of.  Whole rounds of longer items leave the longest alone
+// (causal, rounded up / by the rule above: B1 H2 12000 d = 64 71 / 119 us, d =
+// 128 106 / 162; B1 H6 4096 36 / 52, 50 / 68; B1 H8 3000 d = 128 43 / 56; it is
+// ahead only where d = 64 stays unsplit, B1 H12 2048 30 / 24).
+SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d, bool hides) {
     SplitChoices r;
     const int64_t wide_items = bh * ((Nq + 255) / 256), items = bh * ((Nq + 127) / 128);
     if (wide_items >= kPrefillSplitBelowItems) return r;
+    if (hides) {
+        const int s = splits_rounded_up(bh, Nq, Nk);
+        if (s > 1) r.c[r.n++] = {s, false};
+        return r;
+    }
     int64_t cap = Nk / kMinKeysPerPrefillSplit;
     if (cap > kMaxSplits) cap = kMaxSplits;
     const auto capped = [&](int64_t s) { return s > cap ? cap : s; };
@@ -107,23 +130,26 @@ SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d
     return r;
 }
 
+bool mask_hides(int64_t Nq, int64_t Nk, bool causal) { return causal && 2 * Nq > Nk; }
+
 // Partial states of a call that splits its keys as often as its 128-query
 // items, rounded up, go into the target: what a workspace had to hold before
 // the choices above, and still suffices for one of them.
 size_t prefill_least_ws_bytes(int64_t bh, int64_t Nq, int64_t Nk, int64_t d) {
     if (bh * ((Nq + 255) / 256) >= kPrefillSplitBelowItems) return 0;
-    const int64_t items = bh * ((Nq + 127) / 128);
-    int64_t s = (kPrefillTargetBlocks + items - 1) / items;
-    const int64_t cap = Nk / kMinKeysPerPrefillSplit;
-    if (s > cap) s = cap;
-    if (s > kMaxSplits) s = kMaxSplits;
-    return s > 1 ? prefill_ws_bytes(bh, Nq, d, (int)s) : 0;
+    const int s = splits_rounded_up(bh, Nq, Nk);
+    return s > 1 ? prefill_ws_bytes(bh, Nq, d, s) : 0;
 }
 
+// The most splits a call of these sizes may make, with the mask or without.
 int pick_prefill_splits(int64_t bh, int64_t Nq, int64_t Nk, int64_t d, int requested) {
     if (requested > 0) return requested;
-    const SplitChoices r = prefill_split_choices(bh, Nq, Nk, d);
-    return r.n ? r.c[0].splits : 1;
+    int s = 1;
+    for (const bool causal : {false, true}) {
+        const SplitChoices r = prefill_split_choices(bh, Nq, Nk, d, mask_hides(Nq, Nk, causal));
+        if (r.n && r.c[0].splits > s) s = r.c[0].splits;
+    }
+    return s;
 }
 
 // Split-K work items (128-query tiles x splits per head slice) must fit the
@@ -322,7 +348,7 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, i
     } else if (!decode && bh > 0 && Nq > 0 && in_dtype == MOA_BF16) {
         // Split-K prefill: explicitly requested splits need the workspace;
         // the automatic choice takes what fits, in the end one pass.
-        const SplitChoices ch = prefill_split_choices(bh, Nq, Nk, dk);
+        const SplitChoices ch = prefill_split_choices(bh, Nq, Nk, dk, mask_hides(Nq, Nk, causal != 0));
         if (num_splits > 0) {
             splits = num_splits;
             wide = ch.n > 0 && ch.c[0].wide && ch.c[0].splits == splits;

@@ -397,3 +397,14 @@ def test_proj_takes_the_workspaces_it_took():
             st = moa.moa_attn_fwd_proj(W0, 2 << 44, 3 << 44, 4 << 44, W0, None, B, N, 64, H, d, 0.1, 0,
                                        moa.MOA_BF16, 5 << 44, size, None)
             assert st == (moa.MOA_ERR_INVALID_ARG if size >= min(old, need) else moa.MOA_ERR_WORKSPACE)
+
+
+def test_prefill_queries_cover_the_causal_choice():
+    # Square grids, whose causal calls keep the split count rounded up: the queries, which do not
+    # know the mask, report at least that (B1 H8 3000 split in two under the mask, not without).
+    for bh, n in ((6, 3000), (8, 3000), (12, 2048), (2, 12000), (1, 5000), (5, 4000)):
+        rounded_up = min(-(-256 // (bh * -(-n // 128))), n // 1024)
+        for d in (64, 128):
+            s = moa.moa_attn_num_splits(1, bh, n, n, d, d, 0)
+            assert s >= rounded_up >= 2
+            assert moa.moa_attn_workspace_bytes(1, bh, n, n, d, d, 0) >= bh * n * s * (d + 2) * 4

@@ -173,3 +173,42 @@ def test_wide_splits_and_smaller_workspaces(case, causal):
     # Asked for explicitly, the automatic split count is the automatic choice.
     a = moa.attn_fwd(tq, tk, tv, causal=causal)
     assert torch.equal(a, moa.attn_fwd(tq, tk, tv, causal=causal, num_splits=splits))
+
+
+def _narrow_starts(splits, renew=False):
+    """First tiles of the references of 128-query split items: two streams per share, each (with
+    `renew`) taking a second reference half way."""
+    def starts(n_kt):
+        out, share = [], -(-n_kt // splits)
+        for lo in range(0, n_kt, share):
+            n = min(n_kt, lo + share) - lo
+            first = (n + 1) // 2
+            for a, m in ((lo, first), (lo + first, n - first)):
+                out += [a] * (m > 0) + [a + (m + 1) // 2] * (renew and m > 1)
+        return out
+    return starts
+
+
+def _check_rounding(H, Nq, Nk, d, causal, starts, tile):
+    """O of a call against the model of its weights' rounding: a small part of the rounding itself
+    (about 1.5e-3; fp32 scores near a tie may round the other way, about 1 in 2^12 with exponents
+    of magnitude 2^5, sqrt(2^-12) of the error, and 3e-4 leaves a factor of three)."""
+    import torch
+    from gpu_util import bf16_weight_model
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((1, H, n, d), device="cuda", generator=g).bfloat16() for n in (Nq, Nk, Nk))
+    o = moa.attn_fwd(q, k, v, causal=causal, out_dtype=torch.float32)
+    for h in (0, H - 1):
+        want = bf16_weight_model(*(t[0, h].double() for t in (q, k, v)), causal, starts, tile)
+        diff = float((o[0, h].double() - want).norm() / want.norm())
+        say(f"  {(H, Nq, Nk, d, causal)} head {h}: {diff:.2e} from the model")
+        assert diff <= 3e-4
+
+
+@pytest.mark.parametrize("case", [(11, 2048, 128), (8, 3000, 128), (6, 3000, 64), (6, 4096, 64)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_causal_square_grids_keep_short_items(case):
+    # Under the mask the items of a square grid differ in length: two splits of 128-query items,
+    # dealt in snake order, not two of 256-query items or none.
+    H, n, d = case
+    _check_rounding(H, n, n, d, True, _narrow_starts(2), 128)
