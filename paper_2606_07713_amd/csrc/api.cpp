@@ -76,14 +76,17 @@ int splits_rounded_up(int64_t bh, int64_t Nq, int64_t Nk) {
 // one whose partial states fit its workspace, or one pass.  `wide`: 256-query
 // items (one key stream each) instead of 128-query items (two streams that
 // meet in the workgroup, so half the partial states for the same number of
-// workgroups).
+// workgroups).  `renew`: fewer key streams per row than 128-query splits
+// rounded up would have, so each takes a second softmax reference (as does one
+// pass, where that is the choice).
 struct SplitChoice {
     int splits;
-    bool wide;
+    bool wide, renew;
 };
 struct SplitChoices {
     SplitChoice c[3];
     int n = 0;
+    bool renew_one_pass = false;
 };
 
 // Narrow items: the splits whose items make one round of the compute units, or
@@ -110,9 +113,10 @@ SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d
     SplitChoices r;
     const int64_t wide_items = bh * ((Nq + 255) / 256), items = bh * ((Nq + 127) / 128);
     if (wide_items >= kPrefillSplitBelowItems) return r;
+    const int up = splits_rounded_up(bh, Nq, Nk);
+    const auto add = [&](int64_t s, bool wide) { r.c[r.n++] = {(int)s, wide, (wide ? s : 2 * s) < 2 * up}; };
     if (hides) {
-        const int s = splits_rounded_up(bh, Nq, Nk);
-        if (s > 1) r.c[r.n++] = {s, false};
+        if (up > 1) add(up, false);
         return r;
     }
     int64_t cap = Nk / kMinKeysPerPrefillSplit;
@@ -123,10 +127,11 @@ SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d
     const auto fits = [&](int64_t s) { return prefill_ws_bytes(bh, Nq, d, (int)s) <= moa::kNoallocScratchBytes; };
     const int64_t wide_cap = d == 64 ? cap / 2 : cap;
     if (Nq > 128 && sw <= wide_cap && sw >= 2 * s1 && sw >= s2 && sw > 1 && fits(sw))
-        r.c[r.n++] = {(int)sw, true};
-    if (200 * s1 < 85 * s2 && s2 > 1 && fits(s2)) r.c[r.n++] = {(int)s2, false};
-    if (s1 > 1) r.c[r.n++] = {(int)s1, false};
-    else if (r.n && r.c[0].wide && sw > 2) r.c[r.n++] = {2, true};
+        add(sw, true);
+    if (200 * s1 < 85 * s2 && s2 > 1 && fits(s2)) add(s2, false);
+    if (s1 > 1) add(s1, false);
+    else if (r.n && r.c[0].wide && sw > 2) add(2, true);
+    r.renew_one_pass = r.n == 0 && up > 1;
     return r;
 }
 
@@ -339,7 +344,7 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, i
 
     const bool decode = (Nq == 1);
     int splits = 1;
-    bool wide = false;
+    bool wide = false, renew = false;
     size_t need = 0;
     if (decode && bh > 0) {
         splits = pick_splits(bh, Nk, num_splits);
@@ -351,16 +356,21 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, i
         const SplitChoices ch = prefill_split_choices(bh, Nq, Nk, dk, mask_hides(Nq, Nk, causal != 0));
         if (num_splits > 0) {
             splits = num_splits;
-            wide = ch.n > 0 && ch.c[0].wide && ch.c[0].splits == splits;
+            if (ch.n > 0 && ch.c[0].splits == splits) {   // the library's choice by name
+                wide = ch.c[0].wide;
+                renew = ch.c[0].renew;
+            }
             if (splits > 1 && !prefill_splits_fit(bh, Nq, splits)) return MOA_ERR_UNSUPPORTED;
             need = splits > 1 ? prefill_ws_bytes(bh, Nq, dk, splits) : 0;
             if (need && !ws_fits(need)) return short_ws;
         }
+        if (num_splits == 0) renew = ch.renew_one_pass;
         for (int i = 0; num_splits == 0 && i < ch.n; ++i) {
             const size_t n = prefill_ws_bytes(bh, Nq, dk, ch.c[i].splits);
             if (!ws_fits(n)) continue;
             splits = ch.c[i].splits;
             wide = ch.c[i].wide;
+            renew = ch.c[i].renew;
             need = n;
             break;
         }
@@ -395,6 +405,7 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, i
     p.lay.H = (int)H;
     p.splits = splits;
     p.split_wide = wide;
+    p.renew = renew;
     p.ws = static_cast<float*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
 

@@ -36,6 +36,7 @@ struct Problem {
     // partial states [bh * nq][splits][d] followed by [bh * nq][splits][2].
     int splits;
     bool split_wide;   // split prefill: 256-query items (else 128-query items)
+    bool renew;        // bf16 prefill in key streams: a second reference in each
     float* ws;
 };
 

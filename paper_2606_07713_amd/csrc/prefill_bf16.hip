@@ -80,7 +80,7 @@ template <int D, bool CAUSAL, bool OUT_BF16, bool KSPLIT, bool STRIDED, bool PAR
 __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     const u16* __restrict__ Q, const u16* __restrict__ K, const u16* __restrict__ V,
     void* __restrict__ Out, float* __restrict__ LSE, int Nq, int Nk, int n_bh, int n_qtiles, float c,
-    Layout L, int n_splits) {
+    Layout L, int n_splits, int renew) {
     const Addr<D, STRIDED> A{L, Nq, Nk};
     using C = Cfg<D>;
     constexpr uint32_t RB = C::ROW_BYTES;
@@ -222,6 +222,9 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     int n_w = max(0, min(g_start + g_count, w_end) - g_start);   // local count
     // A split item's waves without queries leave the SIMD to their partners.
     if (PARTIAL && !KSPLIT && wave_q_first >= Nq) n_w = 0;
+    // The local tile at which the rows take a second reference (`renew`; see
+    // launch_persistent).
+    const int t_renew = renew ? max(1, (g_count + 1) / 2) : g_count;
 
     // ---- a2: direct-to-LDS tile loads.  Lane l of the i-th load of loader lw
     // fills slot S = (lw*LPW + i)*64 + l of its stream's tile, which holds
@@ -359,8 +362,9 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
 
     // Step I on the tile: its row max; the reference is raised (and l, O owe
     // the factor 2^(m_old - m_new)) only when the tile exceeds it by more than
-    // kRescaleSlack.
-    auto raise_reference = [&]() {
+    // kRescaleSlack.  `anew`: from here on the reference follows this tile, up
+    // or (by at most kRenewDrop) down.
+    auto raise_reference = [&](bool anew) {
         // The empty asm keeps the max from being hoisted onto the fast path
         // (the scores do not change between the passes below).
         float mx = kNegInf;
@@ -370,11 +374,11 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[kb][i]);
         const float mt = half_max(mx) * c;
-        if (wave_any(mt > m_run + kRescaleSlack)) {
+        if (anew || wave_any(mt > m_run + kRescaleSlack)) {
             // A row may have seen no visible key yet (its reference is still
             // -inf): there is nothing to rescale, and 2^(-inf - -inf) must
             // not be formed.
-            const float m_new = fmaxf(m_run, mt + kRefHeadroom);
+            const float m_new = fmaxf(anew ? m_run - kRenewDrop : m_run, mt + kRefHeadroom);
             const float alpha = (m_run == kNegInf) ? 0.0f : exp2_hw(m_run - m_new);
             l_run *= alpha;
             alpha_pend = rescale_pend ? alpha_pend * alpha : alpha;
@@ -403,10 +407,11 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     auto softmax_phase = [&](int t) {
         if (t >= n_w) return;
         if (tile_needs_mask(t)) apply_mask(t);
-        if (wave_any(m_run == kNegInf)) raise_reference();
+        const bool anew = (KSPLIT || PARTIAL) && t == t_renew;
+        if (anew || wave_any(m_run == kNegInf)) raise_reference(anew);
         float part = exp_pack(neg_m);
         if (wave_any(!(part <= kFastSumLimit))) {
-            raise_reference();
+            raise_reference(false);
             part = exp_pack(neg_m);
         }
         l_run += part;
@@ -689,6 +694,11 @@ bool use_indep(long long items256, long long items128, int nq, int nk, int cus) 
 // One persistent launch: as many workgroups as the device holds at once, at
 // most one per work item.  `n_qtiles` counts query tiles times key splits;
 // `out` and `lse` are O and LSE, or the two partial-state arrays (PARTIAL).
+// With Problem::renew every key stream takes a second softmax reference half
+// way: the weight of a reference's own score is a power of two, exact in bf16,
+// and a call with fewer streams per row than two per 128-query split, rounded
+// up to the target, had an error against fp64 of up to 1.8% more (41 heads 18
+// x 15038 d = 128).
 template <int D, bool CAUSAL, bool OUT_BF16, bool KSPLIT, bool STRIDED, bool PARTIAL = false>
 hipError_t launch_persistent(const Problem& p, int n_qtiles, float c, void* out, float* lse,
                              int n_splits, hipStream_t stream) {
@@ -706,7 +716,7 @@ hipError_t launch_persistent(const Problem& p, int n_qtiles, float c, void* out,
     return launch_kernel(kernel, dim3(grid), dim3(THREADS), stream,
                          static_cast<const u16*>(p.q), static_cast<const u16*>(p.k),
                          static_cast<const u16*>(p.v), out, lse, p.nq, p.nk, p.bh, n_qtiles, c,
-                         p.lay, n_splits);
+                         p.lay, n_splits, p.renew ? 1 : 0);
 }
 
 template <int D, bool CAUSAL, bool OUT_BF16, bool STRIDED>

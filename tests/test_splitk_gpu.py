@@ -212,3 +212,34 @@ def test_causal_square_grids_keep_short_items(case):
     # dealt in snake order, not two of 256-query items or none.
     H, n, d = case
     _check_rounding(H, n, n, d, True, _narrow_starts(2), 128)
+
+
+def _wide_starts(splits):
+    """First tiles of the references of 256-query split items: one stream per share, two each."""
+    def starts(n_kt):
+        out, share = [], -(-n_kt // splits)
+        for lo in range(0, n_kt, share):
+            n = min(n_kt, lo + share) - lo
+            out += [lo] + [lo + (n + 1) // 2] * (n > 1)
+        return out
+    return starts
+
+
+@pytest.mark.parametrize("case", [(41, 18, 15038, 128, True, 6), (40, 36, 7362, 64, True, 6),
+                                  (11, 2048, 2048, 64, False, 1), (6, 3000, 3000, 128, False, 1)],
+                         ids=lambda s: "x".join(str(int(x)) for x in s))
+def test_fewer_splits_take_second_references(case):
+    # Fewer splits than 128-query items rounded up to the target would have (one pass among them):
+    # every key stream takes a second reference half way.
+    H, Nq, Nk, d, causal, splits = case
+    _check_rounding(H, Nq, Nk, d, causal, _narrow_starts(splits, renew=True), 128)
+
+
+@pytest.mark.parametrize("case", [(60, 130, 4100, 128, False, 4), (34, 206, 20568, 64, True, 7),
+                                  (60, 300, 4500, 128, True, 2)],
+                         ids=lambda s: "x".join(str(int(x)) for x in s))
+def test_wide_splits_take_second_references(case):
+    # 256-query items hold one stream where two 128-query items hold two: the same.
+    H, Nq, Nk, d, causal, splits = case
+    assert moa.moa_attn_num_splits(1, H, Nq, Nk, d, d) == splits
+    _check_rounding(H, Nq, Nk, d, causal, _wide_starts(splits), 256)
