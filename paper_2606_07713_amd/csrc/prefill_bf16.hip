@@ -672,19 +672,21 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 //     d 64:  290 x 300 30.0 / 17.8; 176 x 777 48.2 / 29.3; 51 x 3000 93.8 / 77.0; 32 x 4096
 //            88.9 / 82.7; 32 x 8192 326 / 303; 8 x 16384 304 / 318
 //     d 128: 290 x 300 41.2 / 28.2; 176 x 777 67.1 / 54.1; 96 x 1024 43.4 / 46.1; 51 x 3000
-//            138 / 157; exactly one item per unit, where the longest sets the time:
-//            16 x 4096 109 / 96, 8 x 8192 208 / 184 (not with strided rows: 110 / 113)
+//            138 / 157; 17 x 4096 111 / 111, 20 x 4096 113 / 129.  With exactly one item
+//            per unit the contiguous layout gains (16 x 4096 110 / 99, 32 x 2048 60 / 55) and
+//            the packed one loses (111 / 114, 61 / 62); the same values in two storages take
+//            one kernel, so that their results are the same bits
 //     key-split grids (fewer 256-query items than units): 127 x 512 d 64 16.9 / 15.1, d 128
 //            26.3 / 22.8; 45 x 777 15.4 / 17.4, 22.7 / 24.0
 // A mask that hides less than a quarter of the scores is treated as none
 // (80 x 700 of 2000: 46.2 / 39.2, 70.4 / 62.8).
-template <int D, bool CAUSAL, bool STRIDED>
+template <int D, bool CAUSAL>
 bool use_indep(long long items256, long long items128, int nq, int nk, int cus) {
     if (items128 <= cus) return false;
     const long long W = (items128 + cus - 1) / cus, r = (items256 + cus - 1) / cus;
     if (CAUSAL && 2LL * nq > nk) {
         if (items256 < cus) return nk <= 512;
-        return D == 64 ? nk <= 8192 : (nk <= 896 || (r == 1 && !STRIDED));
+        return nk <= (D == 64 ? 8192 : 896);
     }
     if (items256 < cus) return D == 128 || nk < 1024 || 2 * items128 <= 3 * cus;
     if (D == 64) return 13 * W < 25 * r;
@@ -741,7 +743,7 @@ hipError_t launch(const Problem& p, hipStream_t stream) {
     if (e != hipSuccess) return e;
     const long long items_pp = (long long)p.bh * qt_pp, items_ks = (long long)p.bh * qt_ks;
     const bool key_split = p.nk > BN && use_key_split<CAUSAL>(items_pp, items_ks, p.nk, cus);
-    if (use_indep<D, CAUSAL, STRIDED>(items_pp, items_ks, p.nq, p.nk, cus))
+    if (use_indep<D, CAUSAL>(items_pp, items_ks, p.nq, p.nk, cus))
         return launch_prefill_indep(p, cus, key_split, stream);
     if (key_split)
         return launch_persistent<D, CAUSAL, OUT_BF16, true, STRIDED>(p, qt_ks, c, p.o, p.lse, 1,

@@ -197,3 +197,30 @@ def test_strided_equals_contiguous_bitwise():
     a = _run(q, k, v, "contiguous", causal=False)
     b = _run(q, k, v, "bshd", causal=False)
     assert np.array_equal(a, b)
+
+
+# One shape per bf16 prefill route (256 compute units), wide logits: the reference is raised at
+# keys of its own in each of them, and sums regroup.
+ROUTES = {
+    "pingpong": (1, 260, 1000, 1000, 128, True),
+    "pingpong_one_item_per_unit": (1, 64, 1024, 1024, 128, True),
+    "pingpong_full": (1, 256, 300, 300, 128, False),
+    "independent": (1, 260, 300, 300, 64, True),
+    "independent_key_split_grid": (1, 123, 364, 364, 128, True),
+    "key_split": (1, 60, 500, 500, 64, False),
+    "split": (1, 4, 300, 5000, 64, True),
+    "split_wide": (1, 60, 130, 4100, 128, False),
+}
+
+
+@pytest.mark.parametrize("route", list(ROUTES))
+def test_strided_equals_contiguous_bitwise_on_every_route(route):
+    import torch
+    import paper_2606_07713_amd as moa
+    B, H, Nq, Nk, d, causal = ROUTES[route]
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((B, H, n, d), device="cuda", generator=g).bfloat16() for n in (Nq, Nk, Nk))
+    bshd = tuple(t.transpose(1, 2).contiguous().transpose(1, 2) for t in (q, k, v))
+    kw = dict(causal=causal, scale=0.7, out_dtype=torch.float32, return_lse=True)
+    for a, b in zip(moa.attn_fwd(q, k, v, **kw), moa.attn_fwd(*bshd, **kw)):
+        assert torch.equal(a, b)
