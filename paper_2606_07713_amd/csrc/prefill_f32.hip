@@ -206,7 +206,7 @@ hipError_t launch_s(const Problem& p, hipStream_t stream) {
 // and multiplies the grid: 16 lanes per row (4 rows per workgroup) are the
 // fastest while that grid fits the compute units, 8 lanes (8 rows) on the next
 // larger grids at d = 128 while the keys are few; everything else belongs to
-// the matrix-core kernel.  us, raw calls, one box:
+// the matrix-core kernel.  us, calls replayed from a graph, one box:
 //
 //                                       16 lanes  8 lanes  matrix cores
 //   B1 H1 128 x 128, d = 64               4.5       5.0       4.5
@@ -217,9 +217,12 @@ hipError_t launch_s(const Problem& p, hipStream_t stream) {
 //   B1 H2 300 x 517, d = 128              13.4      17.1      15.7
 //   B1 H1 1K x 1K causal, d = 128         22.8      -         25.1
 //   B1 H16 128 x 128 causal, d = 128      -         7.0       7.3
+//   B1 H10 160 x 160, d = 128             -         7.8       8.5  (causal 7.5 / 8.6)
+//   B1 H8 211 x 211, d = 128              -         9.5       9.9  (causal 9.0 / 9.8)
+//   B1 H5 256 x 256, d = 128              -         10.6      10.0
 //   B1 H20 128 x 128, d = 64              -         -         4.6 (8 streams of 16 rows: 6.7)
 //   B1 H8 256 x 256, d = 128              -         11.1      9.8
-//   B1 H1 2K x 2K causal, d = 128         56.2      56.5      43.4
+//   B1 H2 2K x 2K causal, d = 128         56.2      56.5      43.4
 template <int D, bool CAUSAL>
 hipError_t launch(const Problem& p, hipStream_t stream) {
     const long long blocks16 = (long long)p.bh * ((p.nq + 15) / 16);
@@ -228,7 +231,7 @@ hipError_t launch(const Problem& p, hipStream_t stream) {
     if (e != hipSuccess) return e;
     if (4 * blocks16 <= cus && (D == 128 || p.nk < 1000)) return launch_s<D, CAUSAL, 16, 16>(p, stream);
     if constexpr (D == 128)
-        if (2 * blocks16 <= cus && p.nk <= 128) return launch_s<D, CAUSAL, 16, 8>(p, stream);
+        if (2 * blocks16 <= cus && p.nk <= 224) return launch_s<D, CAUSAL, 16, 8>(p, stream);
     return launch_prefill_f32_mfma(p, cus, stream);
 }
 

@@ -35,3 +35,18 @@ def test_f32_matrix_core_prefill(shape):
     ref, ref_lse = oracle_full(q, k, v, causal=causal, with_lse=True)
     assert max_err(o, ref) <= TOL["f32"]
     assert max_err(lse, ref_lse) <= 1e-5 * max(1.0, np.abs(ref_lse).max())
+
+
+# d = 128, 65 to 128 tiles of 16 rows: 8 lanes per row up to 224 keys, the matrix cores beyond.
+@pytest.mark.parametrize("shape", [(1, 5, 211, 211), (2, 4, 200, 224), (1, 8, 250, 225), (3, 4, 97, 160)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+def test_f32_eight_lanes_per_row(shape, causal):
+    B, H, Nq, Nk = shape
+    if causal and Nq > Nk:
+        pytest.skip("causal requires Nq <= Nk")
+    q, k, v = gen(B, H, Nq, Nk, 128, "f32", seed=sum(shape))
+    o, lse = run_gpu(q, k, v, causal=causal, return_lse=True)
+    ref, ref_lse = oracle_full(q, k, v, causal=causal, with_lse=True)
+    assert max_err(o, ref) <= TOL["f32"]
+    assert max_err(lse, ref_lse) <= 1e-5 * max(1.0, np.abs(ref_lse).max())
