@@ -177,3 +177,29 @@ def test_projection_wide_tiles(pairs):
         absum = (x.double().abs().view(-1, Dm) @ w.double().abs().t().contiguous()).view(B, N, H, d).transpose(1, 2)
         err = (got.double() - want).abs()
         assert bool((err <= want.abs() * 2.0 ** -7 + Dm * 2.0 ** -23 * absum).all())
+
+
+def test_projection_rows_past_a_descriptor():
+    # Dm = 2^27: 16 rows pass 4 GiB, and the kernel takes 64-bit row offsets.  The weights (17 GB, one
+    # tensor for all three) are zero but for a few hundred columns over the whole length, X also holds
+    # values where they are zero; a wrong row or column would be seen.
+    import torch
+    import paper_2606_07713_amd as moa
+    N, Dm, H, d = 3, 1 << 27, 1, 64
+    say("  17 GB of weights")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    edges = [0, 1, 31, 32, 63, 64, 127, 1 << 26, (1 << 26) - 1, Dm - 65, Dm - 64, Dm - 33, Dm - 32, Dm - 1]
+    ks = torch.tensor(sorted(set(edges) | set(torch.randint(0, Dm, (300,), device="cuda", generator=g).tolist())),
+                      device="cuda")
+    w = torch.zeros((H * d, Dm), dtype=torch.bfloat16, device="cuda")
+    x = torch.zeros((1, N, Dm), dtype=torch.bfloat16, device="cuda")
+    x[:, :, torch.randint(0, Dm, (5000,), device="cuda", generator=g)] = 100.0
+    w[:, ks] = torch.randn((H * d, ks.numel()), device="cuda", generator=g).bfloat16() / 16
+    x[:, :, ks] = torch.randn((1, N, ks.numel()), device="cuda", generator=g).bfloat16()
+    say("  projection")
+    _, qkv = moa.attn_fwd_proj(x, w, w, w, H, return_qkv=True)
+    xs, wt = x[0][:, ks].double(), w[:, ks].double().t().contiguous()
+    want, absum = xs @ wt, xs.abs() @ wt.abs()
+    for got in qkv:
+        err = (got[0, 0].double() - want).abs()
+        assert bool((err <= want.abs() * 2.0 ** -7 + ks.numel() * 2.0 ** -23 * absum).all())
