@@ -171,10 +171,11 @@ def test_bwd_many_items_selected_heads():
         _check(tuple(g[sl] for g in got), ref, _bounds(qs, ks, vs, gs, scale, True), TOL_ISOLATED)
 
 
-# Item sizes by grid (256 compute units): 256 heads of at most 256 rows take 256-query items without
-# the mask (128-query ones under it), 256-key items at d = 64 and 128-key items at d = 128; 16 heads
-# of 600 take 128-query items in two key streams with 128-key items (without the mask) or 64-key
-# items in two query streams (with it).  Lengths one past a tile, odd first steps, Nq < Nk.
+# Item sizes by grid (256 compute units).  dQ: 256 heads take 256-query items, 97 rows without the
+# mask 128-query items in two key streams, as do 16 heads.  dK, dV: 256 heads of up to 257 keys take
+# 256-key items at d = 64 (with the mask, the first step of every pair even) and 128-key items at d =
+# 128 (with the mask, odd first steps), 16 heads 64-key items in two query streams.  Lengths one past
+# a tile, Nq < Nk.
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("shape,scale", [((8, 32, 129, 129, 64), 0.125), ((8, 32, 97, 130, 64), -0.2),
                                          ((8, 32, 130, 257, 64), 0.125), ((8, 32, 129, 161, 128), 0.09),
@@ -189,6 +190,25 @@ def test_bwd_item_sizes(shape, scale, causal):
         qs, ks, vs, gs = (a[sl] for a in (q, k, v, do))
         ref = oracle.attention_bwd(qs, ks, vs, gs, scale=scale, causal=causal)
         _check(tuple(g[sl] for g in got), ref, _bounds(qs, ks, vs, gs, scale, causal), TOL_ISOLATED)
+
+
+# 32 heads of 1000, d = 64: dQ in 128-query items, dK, dV in 128-key items of one query stream (with
+# the mask, odd first steps).  256 heads, 161 keys: 256-key items whose first step is odd under the
+# mask (query 32 is the first to see key 64).
+@pytest.mark.parametrize("grad_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("shape", [(4, 8, 1000, 1000, 64), (8, 32, 129, 161, 64)])
+def test_bwd_key_items_d64(shape, causal, grad_dtype):
+    B, H, Nq, Nk, d = shape
+    q, k, v, do = _inputs(B, H, Nq, Nk, d, _seed("key items", shape, causal))
+    o, lse = oracle.attention(q, k, v, scale=0.125, causal=causal, with_lse=True)
+    got = _gpu_bwd(q, k, v, do, o, lse, 0.125, causal, grad_dtype=grad_dtype)
+    for b, h in ((0, 0), (B - 1, H - 1), (B // 2, 1)):
+        sl = (slice(b, b + 1), slice(h, h + 1))
+        qs, ks, vs, gs = (a[sl] for a in (q, k, v, do))
+        ref = oracle.attention_bwd(qs, ks, vs, gs, scale=0.125, causal=causal)
+        _check(tuple(g[sl] for g in got), ref, _bounds(qs, ks, vs, gs, 0.125, causal), TOL_ISOLATED,
+               bf16_store=grad_dtype == "bf16")
 
 
 def test_bwd_deterministic():
