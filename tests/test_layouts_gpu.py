@@ -1,8 +1,8 @@
 """Strided layouts on the GPU (moa_attn_fwd_strided through attn_fwd): the same
 seeded inputs stored as [B, N, H, d] views, packed QKV buffers, padded rows and
 K/V shared by every head, against the oracle on the contiguous arrays.  Every
-kernel family is covered: the two bf16 prefill layouts (ping-pong on a large
-and on a mid-size grid, key split on a small one), fp32 prefill and decode.  The layouts are the
+kernel family is covered: bf16 prefill (ping-pong, independent workgroups, key split, split
+items), fp32 prefill and decode.  The layouts are the
 storage functions of the footnote to eq. gamma with per-dimension strides.
 
 Layouts with a strided head dimension -- column-major heads ([B][H][d][N]),
@@ -105,8 +105,10 @@ def _inputs(B, H, Nq, Nk, d, dtype, layout, seed):
 
 # (B, H, Nq, Nk, d, dtype): kernel family each exercises
 SHAPES = {
-    "pingpong": (2, 128, 1000, 1000, 64, "bf16"),    # 1024 items of 256 queries
-    "pingpong_mid": (1, 128, 600, 600, 128, "bf16"), # 384 items: 1.5 per compute unit
+    "pingpong": (2, 128, 1000, 1000, 64, "bf16"),    # 1024 items of 256 queries (masked:
+                                                     #   independent workgroups)
+    "pingpong_mid": (1, 128, 600, 600, 128, "bf16"), # 384 items, 1.5 per compute unit:
+                                                     #   independent workgroups
     "keysplit": (2, 4, 300, 300, 128, "bf16"),       # 16 items
     "f32": (2, 3, 100, 100, 64, "f32"),              # fp32 kernels by grid size: vector ALU,
     "f32_mid": (1, 6, 300, 300, 64, "f32"),          #   matrix cores in 4 key streams,
@@ -197,6 +199,33 @@ def test_strided_equals_contiguous_bitwise():
     a = _run(q, k, v, "contiguous", causal=False)
     b = _run(q, k, v, "bshd", causal=False)
     assert np.array_equal(a, b)
+
+
+# Strided rows on the ping-pong layout at d = 128 and d = 64, masked, and on split items of 256 queries.
+STRIDED_CASES = {
+    "pingpong_d128": (2, 20, 1800, 1800, 128, True),
+    "pingpong_d64": (1, 8, 8300, 8300, 64, True),
+    "split_wide_d128": (1, 60, 130, 4100, 128, False),
+    "split_wide_d64": (1, 60, 130, 8200, 64, True),
+    "split_wide_square": (1, 11, 2048, 2048, 128, False),
+}
+
+
+@pytest.mark.parametrize("case", list(STRIDED_CASES))
+@pytest.mark.parametrize("layout", ["bshd", "padded", "packed", "shared_kv"])
+def test_strided_rows_on_large_items(case, layout):
+    B, H, Nq, Nk, d, causal = STRIDED_CASES[case]
+    if layout == "packed" and Nq != Nk:
+        pytest.skip("packed QKV needs Nq == Nk")
+    q, k_dev, v_dev, k, v = _inputs(B, H, Nq, Nk, d, "bf16", layout, _seed("large", case, layout))
+    o, lse = _run(q, k_dev, v_dev, layout, out_layout="bshd", causal=causal, out_dtype="f32", return_lse=True)
+    assert not np.isnan(o).any()
+    rows = sample_rows(B, H, Nq, 128, seed=21, tile=256)
+    ref, ref_lse = oracle.attention_rows(q, k, v, rows, causal=causal, with_lse=True)
+    err = max_err(o.reshape(-1, d)[rows], ref)
+    say(f"{case} {layout}: max err {err:.3e}")
+    assert err <= TOL["bf16"]
+    assert max_err(lse.reshape(-1)[rows], ref_lse) <= 4e-3 + 1e-5 * np.abs(ref_lse).max()
 
 
 # One shape per bf16 prefill route (256 compute units), wide logits: the reference is raised at

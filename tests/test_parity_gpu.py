@@ -70,10 +70,10 @@ def _lse_tol(dtype, ref_lse):
     return 4e-3 + 1e-5 * np.abs(ref_lse).max()
 
 
-# Grids of at least one 256-query item per compute unit (256 on MI355X) take
-# the ping-pong layout, and the smaller prefill shapes above the key-split
-# layout.  These cover the ping-pong layout with ragged query and key tails,
-# on sampled rows.
+# Grids of more 256-query items than compute units (256 on MI355X), with
+# ragged query and key tails, on sampled rows: the ping-pong layout, except the
+# first under the mask (independent workgroups).  The smaller prefill shapes
+# above take the key split.
 PINGPONG_SHAPES = [
     # B, H, Nq, Nk, d
     (4, 64, 1000, 1000, 64),
@@ -98,8 +98,8 @@ def test_prefill_pingpong_layout_sampled(shape, causal):
 
 MID_SHAPES = [
     # B, H, Nq, Nk, d: from one 256-query item per compute unit up to a few per unit, where the
-    # layout choice weighs the ping-pong layout against the key split (uneven rounds of
-    # equal-cost items without the mask); ragged query and key counts
+    # layout choice weighs the ping-pong layout, the key split and independent workgroups (uneven
+    # rounds of equal-cost items without the mask); ragged query and key counts
     (2, 64, 1000, 1000, 64),
     (1, 128, 600, 700, 128),
     (4, 16, 1024, 1024, 128),
@@ -135,6 +135,33 @@ def test_prefill_mid_grid_bf16_out(causal):
     err = max_err(o.reshape(-1, d)[rows], ref)
     say(f"prefill mid-size grid bf16 out causal={causal}: max err {err:.3e}")
     assert err <= TOL["bf16"]
+
+
+# The ping-pong layout under the mask (d = 64: beyond 8192 keys, d = 128: beyond 896) and without
+# it on exactly one item per compute unit; its scales, and logits wide enough that the reference is
+# raised again and again.
+PINGPONG_CASES = [
+    # B, H, Nq, Nk, d, causal
+    (1, 8, 8300, 8300, 64, True),
+    (2, 20, 1800, 1900, 128, True),
+    (1, 256, 250, 300, 64, False),
+    (1, 256, 256, 300, 128, False),
+]
+
+
+@pytest.mark.parametrize("case", PINGPONG_CASES, ids=lambda s: "x".join(str(int(x)) for x in s))
+@pytest.mark.parametrize("scale", [None, -0.3, 4.0])
+@pytest.mark.parametrize("out_dtype", ["bf16", "f32"])
+def test_pingpong_masks_and_scales(case, scale, out_dtype):
+    B, H, Nq, Nk, d, causal = case
+    q, k, v = gen(B, H, Nq, Nk, d, "bf16", seed=_seed("ping-pong", case))
+    o, lse = run_gpu(q, k, v, causal=causal, scale=scale, out_dtype=out_dtype, return_lse=True)
+    rows = sample_rows(B, H, Nq, 160, seed=7, tile=256)
+    ref, ref_lse = oracle.attention_rows(q, k, v, rows, causal=causal, scale=scale, with_lse=True)
+    err = max_err(o.reshape(-1, d)[rows], ref)
+    say(f"ping-pong {case} scale {scale}: max err {err:.3e}")
+    assert err <= TOL["bf16"]
+    assert max_err(lse.reshape(-1)[rows], ref_lse) <= _lse_tol("bf16", ref_lse)
 
 
 DECODE_CASES = [
@@ -180,7 +207,9 @@ def test_unusual_scales(scale, dtype, nq):
 @pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
 def test_negative_scale_layouts(shape, causal):
     # A negative scale flips the sign of Q inside the kernels (after Q is
-    # loaded); every bf16 prefill layout, sampled rows of the larger two.
+    # loaded): the key split, independent workgroups, and the ping-pong layout
+    # (without the mask; with it independent workgroups again), sampled rows of
+    # the larger two.
     B, H, Nq, Nk, d = shape
     q, k, v = gen(B, H, Nq, Nk, d, "bf16", seed=_seed("neg", shape, causal))
     o = run_gpu(q, k, v, causal=causal, scale=-0.3, out_dtype="f32")
@@ -191,8 +220,8 @@ def test_negative_scale_layouts(shape, causal):
     assert err <= TOL["bf16"]
 
 
-# Key-split (4 items) and ping-pong (512 and 1024 items) layouts; the two
-# larger grids are checked on sampled rows.
+# Key split (4 items), and the ping-pong layout (512 and 1024 items; independent
+# workgroups under the mask); the two larger grids are checked on sampled rows.
 EXTREME_SHAPES = [
     # B, H, Nq, Nk, d
     (2, 2, 77, 700, 128),

@@ -141,7 +141,8 @@ WIDE = [
     # B, H, Nq, Nk, d: 256-query split items (two to a narrow one); ragged rows and keys
     (2, 30, 130, 4100, 128),
     (1, 32, 200, 8200, 128),
-    (1, 16, 257, 8200, 64),
+    (1, 16, 257, 8200, 64),     # narrow items: too few keys for wide ones at d = 64
+    (1, 60, 130, 8200, 64),
 ]
 
 
