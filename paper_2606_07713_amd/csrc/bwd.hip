@@ -135,16 +135,12 @@ __device__ __forceinline__ void buffer_load16_to_lds_untracked(u32x4 rsrc, uint3
 template <int D, int NW, int ROWS = BN>
 struct DmaStager {
     static constexpr int STAGE_BYTES = ROWS * Cfg<D>::ROW_BYTES;
-    static constexpr bool PART = STAGE_BYTES < NW * 1024;          // only the first waves load
-    static constexpr int LPS = PART ? 1 : STAGE_BYTES / (NW * 1024);
-    static_assert(STAGE_BYTES % 1024 == 0 && (PART || STAGE_BYTES % (NW * 1024) == 0),
-                  "a stage must split into wave loads");
-    bool on = true;          // this wave loads
+    static constexpr int LPS = STAGE_BYTES / (NW * 1024);
+    static_assert(STAGE_BYTES % (NW * 1024) == 0, "a stage must split into wave loads");
     uint32_t goff[LPS];
     uint32_t lds_off;        // this wave's first 1 KB of a stage
     __device__ __forceinline__ DmaStager(int wave, int lane) {
         lds_off = (uint32_t)wave * LPS * 1024u;
-        if (PART) on = wave < STAGE_BYTES / 1024;
 #pragma unroll
         for (int i = 0; i < LPS; ++i) {
             const int slot = (wave * LPS + i) * 64 + lane;
@@ -152,10 +148,9 @@ struct DmaStager {
             goff[i] = (uint32_t)row * Cfg<D>::ROW_BYTES + (uint32_t)((p ^ swz<D>(row)) * 16);
         }
     }
-    // Rows j*64 .. j*64 + 63 of a head slice of `n` rows into `stage`; rows
-    // past n are zero.
+    // Rows j * ROWS .. of a head slice of `n` rows into `stage`; rows past n
+    // are zero.
     __device__ __forceinline__ void issue(const u16* head, int n, int j, unsigned char* stage) const {
-        if (PART && !on) return;
         const int r0 = min(j * ROWS, n);
         const u32x4 r = rsrc_words(head + (size_t)r0 * D, (uint32_t)(n - r0) * Cfg<D>::ROW_BYTES);
         const uint32_t base = lds_address(stage) + lds_off;

@@ -22,21 +22,20 @@
 namespace moa {
 namespace {
 
+constexpr int STREAMS = 16;       // waves of a workgroup, one key stream each
+constexpr int THREADS = 64 * STREAMS;
 constexpr int ROUND_KEYS = 128;   // keys per round of all streams (STREAMS x KT)
 
 // QL lanes share a query row (they split d); a wave holds 64 / QL rows, and
 // every wave of a workgroup holds the same rows.
 template <int QL>
 constexpr int rows_of() { return 64 / QL; }
-template <int STREAMS>
-constexpr int threads_of() { return 64 * STREAMS; }
 
-template <int D, bool CAUSAL, int STREAMS, int QL>
-__global__ __launch_bounds__(threads_of<STREAMS>()) void prefill_f32_kernel(
+template <int D, bool CAUSAL, int QL>
+__global__ __launch_bounds__(THREADS) void prefill_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     float* __restrict__ Out, float* __restrict__ LSE, int Nq, int Nk, int n_qtiles, float c,
     Layout L) {
-    constexpr int THREADS = threads_of<STREAMS>();
     constexpr int ROWS = rows_of<QL>();
     constexpr int KT = ROUND_KEYS / STREAMS;   // keys per tile
     constexpr int CH = D / (4 * QL);   // float4 chunks per lane (chunk j*QL + quad)
@@ -190,13 +189,13 @@ __global__ __launch_bounds__(threads_of<STREAMS>()) void prefill_f32_kernel(
     }
 }
 
-template <int D, bool CAUSAL, int STREAMS, int QL>
+template <int D, bool CAUSAL, int QL>
 hipError_t launch_s(const Problem& p, hipStream_t stream) {
     constexpr int ROWS = rows_of<QL>();
     const int n_qtiles = (p.nq + ROWS - 1) / ROWS;
     const long long blocks = (long long)p.bh * n_qtiles;
-    return launch_kernel(prefill_f32_kernel<D, CAUSAL, STREAMS, QL>, dim3((unsigned)blocks),
-                         dim3(threads_of<STREAMS>()), stream, static_cast<const float*>(p.q),
+    return launch_kernel(prefill_f32_kernel<D, CAUSAL, QL>, dim3((unsigned)blocks),
+                         dim3(THREADS), stream, static_cast<const float*>(p.q),
                          static_cast<const float*>(p.k), static_cast<const float*>(p.v),
                          static_cast<float*>(p.o), p.lse, p.nq, p.nk, n_qtiles,
                          p.scale * kLog2e, p.lay);
@@ -229,9 +228,9 @@ hipError_t launch(const Problem& p, hipStream_t stream) {
     int cus = 0;
     const hipError_t e = pf::device_cus(stream, cus);
     if (e != hipSuccess) return e;
-    if (4 * blocks16 <= cus && (D == 128 || p.nk < 1000)) return launch_s<D, CAUSAL, 16, 16>(p, stream);
+    if (4 * blocks16 <= cus && (D == 128 || p.nk < 1000)) return launch_s<D, CAUSAL, 16>(p, stream);
     if constexpr (D == 128)
-        if (2 * blocks16 <= cus && p.nk <= 224) return launch_s<D, CAUSAL, 16, 8>(p, stream);
+        if (2 * blocks16 <= cus && p.nk <= 224) return launch_s<D, CAUSAL, 8>(p, stream);
     return launch_prefill_f32_mfma(p, cus, stream);
 }
 
