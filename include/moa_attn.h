@@ -308,7 +308,7 @@ size_t moa_attn_bwd_workspace_bytes(int64_t B, int64_t H, int64_t Nq, int64_t Nk
  * bf16 matrix cores with fp32 accumulation; P and dS are rounded to bf16
  * before they multiply dO, K and Q; exponentials and D are fp32.  Each
  * gradient row is owned by one workgroup: no atomics, and the results are
- * deterministic.  Three kernels are enqueued on `stream`.
+ * deterministic.  Two kernels are enqueued on `stream` (one when Nq == 0).
  *
  * Returns MOA_OK once the work is enqueued (or when B*H == 0: nothing is
  * launched; when Nq == 0, dK and dV are zero-filled), else a MOA_ERR_* code.

@@ -139,7 +139,11 @@ bool mask_hides(int64_t Nq, int64_t Nk, bool causal) { return causal && 2 * Nq >
 
 // Partial states of a call that splits its keys as often as its 128-query
 // items, rounded up, go into the target: what a workspace had to hold before
-// the choices above, and still suffices for one of them.
+// the choices above.  It still suffices for one of them, except where three
+// narrow splits in two rounds are the only one (129 to 170 items): those calls
+// run in one pass, faster there than the two splits the workspace holds (B1 H5
+// 4000 d = 64 45.3 us against 55.9; three splits 45.1; B1 H6 3500 d = 128 57.3
+// against 71.9; 53.5).
 size_t prefill_least_ws_bytes(int64_t bh, int64_t Nq, int64_t Nk, int64_t d) {
     if (bh * ((Nq + 255) / 256) >= kPrefillSplitBelowItems) return 0;
     const int s = splits_rounded_up(bh, Nq, Nk);

@@ -660,8 +660,8 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 // layout / independent:
 //   unmasked, fewer 256-query items than units but more than one 128-query
 //   item each (the key split would need two rounds):
-//     120 x 300 d 64 14.5 / 11.7, d 128 21.0 / 16.7; 40 x 1100 28.8 / 27.0, 43.8 / 39.5;
-//     45 x 1100 29.7 / 30.5, 50.3 / 42.8
+//     120 x 300 d 64 14.8 / 12.3, d 128 22.2 / 19.4; 40 x 1100 30.2 / 29.4, 45.3 / 43.4;
+//     45 x 1100 29.7 / 30.5, 50.0 / 46.7
 //   unmasked, more: W, r
 //     d 64:  69 x 777 [2, 2] 37.8 / 21.8; 96 x 777 [3, 2] 37.5 / 28.2; 73 x 1500 [4, 2]
 //            61.1 / 65.2; 102 x 1500 [5, 3] 94.1 / 78.8; 119 x 1500 [6, 3] 95.8 / 96.4
@@ -669,17 +669,17 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 //            58.9 / 64.9; 102 x 1500 [5, 3] 145 / 148; where the key split applies it is
 //            ahead from 3000 keys on (26 x 3000 [3, 2] 150 / 161)
 //   causal (the ping-pong's 256-query items also compute more of the masked corner):
-//     d 64:  290 x 300 30.0 / 17.8; 176 x 777 48.2 / 29.3; 51 x 3000 93.8 / 77.0; 32 x 4096
+//     d 64:  290 x 300 30.1 / 18.6; 176 x 777 47.8 / 30.7; 51 x 3000 93.8 / 77.0; 32 x 4096
 //            88.9 / 82.7; 32 x 8192 326 / 303; 8 x 16384 304 / 318
-//     d 128: 290 x 300 41.2 / 28.2; 176 x 777 67.1 / 54.1; 96 x 1024 43.4 / 46.1; 51 x 3000
+//     d 128: 290 x 300 41.6 / 29.2; 176 x 777 70.0 / 58.3; 96 x 1024 43.4 / 46.1; 51 x 3000
 //            138 / 157; 17 x 4096 111 / 111, 20 x 4096 113 / 129.  With exactly one item
 //            per unit the contiguous layout gains (16 x 4096 110 / 99, 32 x 2048 60 / 55) and
 //            the packed one loses (111 / 114, 61 / 62); the same values in two storages take
 //            one kernel, so that their results are the same bits
-//     key-split grids (fewer 256-query items than units): 127 x 512 d 64 16.9 / 15.1, d 128
-//            26.3 / 22.8; 45 x 777 15.4 / 17.4, 22.7 / 24.0
+//     key-split grids (fewer 256-query items than units): 127 x 512 d 64 16.5 / 14.8, d 128
+//            26.7 / 23.9; 45 x 777 15.4 / 17.4, 22.7 / 24.0
 // A mask that hides less than a quarter of the scores is treated as none
-// (80 x 700 of 2000: 46.2 / 39.2, 70.4 / 62.8).
+// (80 x 700 of 2000 d 128: 69.0 / 65.7).
 template <int D, bool CAUSAL>
 bool use_indep(long long items256, long long items128, int nq, int nk, int cus) {
     if (items128 <= cus) return false;

@@ -13,8 +13,9 @@
 // 64: 150 us both).  Its gain is the grain: a compute unit takes 128 queries at
 // a time instead of 256, so grids of one and a half rounds do not pay for two,
 // causal items reach less far past the diagonal, and a wave without queries
-// costs nothing.  B8 H12 777 d = 64: 39.1 -> 28.2 us (380 -> 527 TFLOP/s),
-// causal in the packed layout 31.2 -> 18.9; d = 128: 57.5 -> 52.5.
+// costs nothing.  B8 H12 777 contiguous, d = 64: 38.4 -> 29.8 us (386 -> 498
+// TFLOP/s), causal 29.6 -> 19.5; d = 128: 56.3 -> 53.1, causal 40.6 -> 35.7; in
+// the packed layout 39.9 -> 30.9, 31.6 -> 20.0, 58.2 -> 57.4 and 41.8 -> 39.3.
 //
 // Registers: S and P are held for 32 keys at a time, which leaves 136 at d = 64,
 // three waves per SIMD without a spill.  Four waves (128 registers, 6 to 12
