@@ -680,16 +680,36 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 //            26.7 / 23.9; 45 x 777 15.4 / 17.4, 22.7 / 24.0
 // A mask that hides less than a quarter of the scores is treated as none
 // (80 x 700 of 2000 d 128: 69.0 / 65.7).
+//
+// An item of 128 queries reads K and V twice as often as one of 256.  Where
+// that shows, the gain in rounds has to be larger (ping-pong / independent):
+//   K and V beyond the last-level cache (256 MB)
+//     d 64:          877 x 158 of 4853 [7, 4] 362 / 405, 538 x 977 of 4773 [17, 9] 965 / 1078;
+//                    766 x 379 of 5484 [9, 6] 670 / 633, 452 x 769 of 5468 [13, 8] 856 / 816
+//     d 64, causal:  283 x 3782 of 6720 [34, 17] 1811 / 1952, 835 x 1500 of 1888 [40, 20]
+//                    614 / 640; 417 x 1810 of 3234 [25, 14] 735 / 697
+//     d 128:         887 x 513 of 2230 [18, 11] 845 / 985, 874 x 336 of 1010 [11, 7] 272 / 299;
+//                    766 x 352 of 658 [9, 6] 172 / 155
+//   d 128, few queries to many keys: 313 x 181 of 870 [3, 2] 57 / 61, 186 x 297 of 589 [3, 2]
+//                    44 / 46, 360 x 157 of 441 [3, 2] 35 / 33; 393 x 328 of 897 [5, 4] 122 / 100
+//   d 128, causal, no gain in rounds: 888 x 469 of 833 [14, 7] 230 / 273, 738 x 229 of 358
+//                    [6, 3] 61 / 65, 452 x 480 of 873 [8, 4] 120 / 132; one round alone gains
+//                    (packed: 128 x 400 [2, 1] 22.4 / 20.6, 256 x 256 [2, 1] 19.0 / 18.4)
+constexpr long long kCacheBytes = 256LL << 20;
+
 template <int D, bool CAUSAL>
-bool use_indep(long long items256, long long items128, int nq, int nk, int cus) {
+bool use_indep(long long items256, long long items128, int nq, int nk, int bh, int cus) {
     if (items128 <= cus) return false;
     const long long W = (items128 + cus - 1) / cus, r = (items256 + cus - 1) / cus;
+    const bool big = 4LL * D * bh * nk > kCacheBytes;   // bytes of K and V
     if (CAUSAL && 2LL * nq > nk) {
         if (items256 < cus) return nk <= 512;
-        return nk <= (D == 64 ? 8192 : 896);
+        if (D == 64) return nk <= 8192 && (!big || 10 * W <= 18 * r);
+        return nk <= 896 && (W < 2 * r || r == 1);
     }
     if (items256 < cus) return D == 128 || nk < 1024 || 2 * items128 <= 3 * cus;
-    if (D == 64) return 13 * W < 25 * r;
+    if (D == 64) return big ? 10 * W <= 17 * r : 13 * W < 25 * r;
+    if ((big && 2 * W > 3 * r) || (nk >= 2LL * nq && 2 * W >= 3 * r)) return false;
     return 3 * W < 5 * r && !use_key_split<CAUSAL>(items256, items128, nk, cus);
 }
 
@@ -743,7 +763,7 @@ hipError_t launch(const Problem& p, hipStream_t stream) {
     if (e != hipSuccess) return e;
     const long long items_pp = (long long)p.bh * qt_pp, items_ks = (long long)p.bh * qt_ks;
     const bool key_split = p.nk > BN && use_key_split<CAUSAL>(items_pp, items_ks, p.nk, cus);
-    if (use_indep<D, CAUSAL>(items_pp, items_ks, p.nq, p.nk, cus))
+    if (use_indep<D, CAUSAL>(items_pp, items_ks, p.nq, p.nk, p.bh, cus))
         return launch_prefill_indep(p, cus, key_split, stream);
     if (key_split)
         return launch_persistent<D, CAUSAL, OUT_BF16, true, STRIDED>(p, qt_ks, c, p.o, p.lse, 1,

@@ -95,3 +95,27 @@ def test_second_reference_on_key_split_grids(shape):
         diff = float((o[0, h].double() - want).norm() / want.norm())
         say(f"  head {h}: {diff:.2e} from the two-reference model")
         assert diff <= 3e-4
+
+
+@pytest.mark.parametrize("shape", [(1, 700, 100, 200, 128, True), (1, 700, 120, 333, 128, False), (1, 700, 300, 300, 64, True)],
+                         ids=lambda s: "x".join(str(int(x)) for x in s))
+def test_rounds_of_resident_workgroups(shape):
+    # More 128-query items than workgroups the GPU holds at a time, the last round partly filled.
+    B, H, Nq, Nk, d, causal = shape
+    q, k, v = gen(B, H, Nq, Nk, d, "bf16", seed=H + Nk)
+    o, lse = run_gpu(q, k, v, causal=causal, out_dtype="f32", return_lse=True)
+    _check(q, k, v, o, lse, causal)
+
+
+# Routes on both sides of the launch rule's lines (256 compute units): K and V beyond 256 MB, few
+# queries to many keys, no gain in rounds.
+@pytest.mark.parametrize("shape", [(1, 877, 158, 1300, 64, False), (1, 766, 260, 1500, 64, False),
+                                   (1, 313, 181, 870, 128, False), (1, 393, 328, 700, 128, False),
+                                   (1, 738, 229, 358, 128, True), (1, 256, 200, 200, 128, True),
+                                   (1, 835, 500, 1300, 64, False)],
+                         ids=lambda s: "x".join(str(int(x)) for x in s))
+def test_lines_of_the_launch_rule(shape):
+    B, H, Nq, Nk, d, causal = shape
+    q, k, v = gen(B, H, Nq, Nk, d, "bf16", seed=H + Nk)
+    o, lse = run_gpu(q, k, v, causal=causal, out_dtype="f32", return_lse=True)
+    _check(q, k, v, o, lse, causal)
