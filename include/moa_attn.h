@@ -91,7 +91,7 @@ size_t moa_attn_workspace_bytes(int64_t B, int64_t H, int64_t Nq, int64_t Nk, in
  * moa_attn_num_splits -- the number of key splits a call with these
  * arguments will use when given moa_attn_workspace_bytes(...) of workspace
  * (decode-shaped calls, and bf16 prefill; 1 = no split).  Neither query knows
- * the mask: where the library's choice for prefill depends on it (Nk < 2 Nq),
+ * the mask: where the library's choice for prefill depends on it (4 Nk < 9 Nq),
  * both report for the larger of the two choices.
  */
 int moa_attn_num_splits(int64_t B, int64_t H, int64_t Nq, int64_t Nk, int64_t dk, int64_t dv,

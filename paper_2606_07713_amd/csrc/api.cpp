@@ -98,17 +98,21 @@ struct SplitChoices {
 // both halves, at least two wide splits to a narrow one, and keys enough
 // (2048 per split at d = 64): B1 H32 200 x 20011 d = 128 108.8 -> 97.8 us, d =
 // 64 60.2 -> 58.2; B2 H8 700 x 9000 d = 128 83.9 -> 72.4; too short, B1 H12
-// 300 x 6000 d = 64: 21.6 narrow, 25.5 wide.  Choices beyond the first stay
+// 300 x 6000 d = 64: 21.6 narrow, 25.5 wide.  At d = 64 two wide splits where
+// one narrow item per query tile fills the round as well only add the states
+// (wide / one pass: B1 H6 4096 53.8 / 42.0, B1 H2 12000 121.7 / 112.5, B1 H16
+// 1572 x 8115 causal 87.3 / 82.0, B1 H41 658 x 15097 152 / 157).  Choices beyond the first stay
 // within the fixed scratch array, so that a call with it and one with the
 // queried workspace take the same.
 //
-// A causal mask that hides more than a quarter of the scores (`hides`) makes
+// A causal mask that hides more than 2/9 of the scores (`hides`) makes
 // items of unequal length, which even out only over several of them per unit:
 // as many 128-query splits as go into the target, rounded up, in the snake
 // order of item_of.  Whole rounds of longer items leave the longest alone
 // (causal, rounded up / by the rule above: B1 H2 12000 d = 64 71 / 119 us, d =
 // 128 106 / 162; B1 H6 4096 36 / 52, 50 / 68; B1 H8 3000 d = 128 43 / 56; it is
-// ahead only where d = 64 stays unsplit, B1 H12 2048 30 / 24).
+// ahead only where d = 64 stays unsplit, B1 H12 2048 30 / 24).  Where the line
+// lies, d = 64: B1 H5 5120 x 11000 93 / 107, B1 H12 2059 x 4862 60 / 54.
 SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d, bool hides) {
     SplitChoices r;
     const int64_t wide_items = bh * ((Nq + 255) / 256), items = bh * ((Nq + 127) / 128);
@@ -126,7 +130,8 @@ SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d
     const int64_t sw = kPrefillTargetBlocks / wide_items;
     const auto fits = [&](int64_t s) { return prefill_ws_bytes(bh, Nq, d, (int)s) <= moa::kNoallocScratchBytes; };
     const int64_t wide_cap = d == 64 ? cap / 2 : cap;
-    if (Nq > 128 && sw <= wide_cap && sw >= 2 * s1 && sw >= s2 && sw > 1 && fits(sw))
+    const bool one_pass = d == 64 && s1 == 1 && sw == 2;
+    if (Nq > 128 && sw <= wide_cap && sw >= 2 * s1 && sw >= s2 && sw > 1 && !one_pass && fits(sw))
         add(sw, true);
     if (200 * s1 < 85 * s2 && s2 > 1 && fits(s2)) add(s2, false);
     if (s1 > 1) add(s1, false);
@@ -135,7 +140,7 @@ SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d
     return r;
 }
 
-bool mask_hides(int64_t Nq, int64_t Nk, bool causal) { return causal && 2 * Nq > Nk; }
+bool mask_hides(int64_t Nq, int64_t Nk, bool causal) { return causal && 9 * Nq > 4 * Nk; }
 
 // Partial states of a call that splits its keys as often as its 128-query
 // items, rounded up, go into the target: what a workspace had to hold before

@@ -208,11 +208,13 @@ hipError_t launch_t(const Problem& p, int splits, float* ws, hipStream_t stream)
     // A wave's iterations over its chunk are a chain of memory latencies.  On
     // a grid of at most one workgroup per compute unit, 8 waves walk a chunk
     // of up to two of their iterations (512 keys at d = 128 in bf16) in half
-    // the links: B1 H32 Nk 4097 16.9 -> 16.0 us, Nk 1000 9.5 -> 8.8.  Longer
-    // chunks have enough loads in flight with 4 waves, which then lose less
-    // to the merge (B1 H32 Nk 16384: 43.3 us against 45.1 with 8), and grids
-    // beyond the compute units gain nothing (B3 H20 Nk 3000 d = 64: 14.6
-    // against 14.9).
+    // the links: B1 H32 d = 128 Nk 1000 7.4 -> 7.2 us, 2048 10.3 -> 9.8, 4096
+    // 15.0 -> 14.6, B1 H8 Nk 8192 12.5 -> 11.7.  Long chunks have enough loads
+    // in flight with 4 waves, which then lose less to the merge (B1 H32 Nk
+    // 16384: 42.6 us against 43.4 with 8); in between, up to four iterations,
+    // 8 waves would still be up to 5% ahead (Nk 4097, 513 keys a chunk, 15.9
+    // against 15.1; 8192 23.4 against 23.1).  Grids beyond the compute units
+    // gain nothing (B1 H60 Nk 3000 d = 64: 13.7 against 13.9).
     int cus = 0;
     hipError_t e = pf::device_cus(stream, cus);
     if (e != hipSuccess) return e;
