@@ -324,25 +324,9 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     // the same p.  exp_pack() returns the tile's partial sum (this lane's 32
     // keys).  Masked scores are -inf and c > 0, so their weight is exactly 0.
     auto exp_pack = [&](float nm) {
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
         float part[2] = {0.0f, 0.0f};
 #pragma unroll
-        for (int kb = 0; kb < BN / 32; ++kb)
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                u32x4 w;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int i = g * 8 + 2 * j;
-                    const float p0 = exp2_hw(__builtin_fmaf(sacc[kb][i], c, nm));
-                    const float p1 = exp2_hw(__builtin_fmaf(sacc[kb][i + 1], c, nm));
-                    const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
-                    w[j] = __builtin_bit_cast(uint32_t, pp);
-                    part[j & 1] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, part[j & 1], false);
-                }
-                pbuf[kb * 2 + g] = __builtin_bit_cast(bf16x8, w);
-            }
+        for (int kb = 0; kb < BN / 32; ++kb) pack_weights(sacc[kb], c, nm, pbuf + 2 * kb, part);
         return part[0] + part[1];
     };
 

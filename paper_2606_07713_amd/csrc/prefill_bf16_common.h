@@ -60,6 +60,27 @@ __device__ __forceinline__ int dv_of(int b, int m) {
     return 32 * b + m;
 }
 
+// Weights 2^(s c + neg_m) of a 32-key step, rounded to bf16, as the P^T
+// operands of its two 16-key chunks; the rounded weights are added to `part`.
+__device__ __forceinline__ void pack_weights(const f32x16& s, float c, float neg_m, bf16x8* pb, float (&part)[2]) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        u32x4 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = g * 8 + 2 * j;
+            const float p0 = exp2_hw(__builtin_fmaf(s[i], c, neg_m));
+            const float p1 = exp2_hw(__builtin_fmaf(s[i + 1], c, neg_m));
+            const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
+            w[j] = __builtin_bit_cast(uint32_t, pp);
+            part[j & 1] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, part[j & 1], false);
+        }
+        pb[g] = __builtin_bit_cast(bf16x8, w);
+    }
+}
+
 // Persistent schedule.  The grid holds as many workgroups as the GPU runs at
 // once (P); workgroup p walks its share of the n_bh * n_qtiles work items
 // (head slice, query tile) and returns when it has none left, so no workgroup

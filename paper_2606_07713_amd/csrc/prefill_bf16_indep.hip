@@ -179,23 +179,8 @@ __global__ __launch_bounds__(IW * 64, (D == 64 ? 3 : 2)) void prefill_indep_kern
                 };
                 bf16x8 pbuf[SN / 16];
                 auto exp_pack = [&]() __attribute__((always_inline)) {
-                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
                     float part[2] = {0.0f, 0.0f};
-#pragma unroll
-                    for (int g = 0; g < 2; ++g) {
-                        u32x4 w;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int i = g * 8 + 2 * j;
-                            const float p0 = exp2_hw(__builtin_fmaf(sacc[i], c, neg_m));
-                            const float p1 = exp2_hw(__builtin_fmaf(sacc[i + 1], c, neg_m));
-                            const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
-                            w[j] = __builtin_bit_cast(uint32_t, pp);
-                            part[j & 1] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, part[j & 1], false);
-                        }
-                        pbuf[g] = __builtin_bit_cast(bf16x8, w);
-                    }
+                    pack_weights(sacc, c, neg_m, pbuf, part);
                     return part[0] + part[1];
                 };
                 // A row's first reference comes from the whole tile, as in the
