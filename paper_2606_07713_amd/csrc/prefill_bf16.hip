@@ -76,7 +76,10 @@ __device__ __forceinline__ void wait_loads_to_lds() {
 //   acc -- to Out = ws_acc [bh*Nq][n_splits][D] and LSE = ws_ml
 //   [bh*Nq][n_splits][2]; launch_split_combine merges the splits.  A share
 //   with no key visible to a row leaves (m, l, acc) = (-inf, 0, 0).
-template <int D, bool CAUSAL, bool OUT_BF16, bool KSPLIT, bool STRIDED, bool PARTIAL = false>
+// RENEW: the kernel looks for the tile of a second reference where `renew` asks
+//   for one (see launch_persistent; a kernel of its own for unsplit calls, which
+//   the look costs 2%).
+template <int D, bool CAUSAL, bool OUT_BF16, bool KSPLIT, bool STRIDED, bool PARTIAL = false, bool RENEW = PARTIAL>
 __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     const u16* __restrict__ Q, const u16* __restrict__ K, const u16* __restrict__ V,
     void* __restrict__ Out, float* __restrict__ LSE, int Nq, int Nk, int n_bh, int n_qtiles, float c,
@@ -391,7 +394,7 @@ __global__ __launch_bounds__(THREADS, 1) void prefill_bf16_kernel(
     auto softmax_phase = [&](int t) {
         if (t >= n_w) return;
         if (tile_needs_mask(t)) apply_mask(t);
-        const bool anew = (KSPLIT || PARTIAL) && t == t_renew;
+        const bool anew = RENEW && t == t_renew;
         if (anew || wave_any(m_run == kNegInf)) raise_reference(anew);
         float part = exp_pack(neg_m);
         if (wave_any(!(part <= kFastSumLimit))) {
@@ -705,10 +708,10 @@ bool use_indep(long long items256, long long items128, int nq, int nk, int bh, i
 // and a call with fewer streams per row than two per 128-query split, rounded
 // up to the target, had an error against fp64 of up to 1.8% more (41 heads 18
 // x 15038 d = 128).
-template <int D, bool CAUSAL, bool OUT_BF16, bool KSPLIT, bool STRIDED, bool PARTIAL = false>
+template <int D, bool CAUSAL, bool OUT_BF16, bool KSPLIT, bool STRIDED, bool PARTIAL = false, bool RENEW = PARTIAL>
 hipError_t launch_persistent(const Problem& p, int n_qtiles, float c, void* out, float* lse,
                              int n_splits, hipStream_t stream) {
-    auto kernel = prefill_bf16_kernel<D, CAUSAL, OUT_BF16, KSPLIT, STRIDED, PARTIAL>;
+    auto kernel = prefill_bf16_kernel<D, CAUSAL, OUT_BF16, KSPLIT, STRIDED, PARTIAL, RENEW>;
     static const int per_cu = [&] {
         int n = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, THREADS, 0) != hipSuccess) n = 1;
@@ -749,6 +752,9 @@ hipError_t launch(const Problem& p, hipStream_t stream) {
     const bool key_split = p.nk > BN && use_key_split<CAUSAL>(items_pp, items_ks, p.nk, cus);
     if (use_indep<D, CAUSAL>(items_pp, items_ks, p.nq, p.nk, p.bh, cus))
         return launch_prefill_indep(p, cus, key_split, stream);
+    if (key_split && p.renew)
+        return launch_persistent<D, CAUSAL, OUT_BF16, true, STRIDED, false, true>(p, qt_ks, c, p.o, p.lse, 1,
+                                                                                  stream);
     if (key_split)
         return launch_persistent<D, CAUSAL, OUT_BF16, true, STRIDED>(p, qt_ks, c, p.o, p.lse, 1,
                                                                      stream);
