@@ -101,9 +101,13 @@ struct SplitChoices {
 // 300 x 6000 d = 64: 21.6 narrow, 25.5 wide.  At d = 64 two wide splits where
 // one narrow item per query tile fills the round as well only add the states
 // (wide / one pass: B1 H6 4096 53.8 / 42.0, B1 H2 12000 121.7 / 112.5, B1 H16
-// 1572 x 8115 causal 87.3 / 82.0, B1 H41 658 x 15097 152 / 157).  Choices beyond the first stay
-// within the fixed scratch array, so that a call with it and one with the
-// queried workspace take the same.
+// 1572 x 8115 causal 87.3 / 82.0, B1 H41 658 x 15097 152 / 157).  Nor do more
+// wide splits help at d = 64 where the narrow ones fill the round as well and
+// fewer than eight heads share the XCDs, up to 16K keys (wide / narrow: B1 H2
+// 8192 59.8 / 55.1, B1 H4 4096 x 8192 53.7 / 51.0, B1 H3 5120 x 9000 56.0 / 53.9;
+// B1 H4 4096 x 16384 89 / 88, x 20000 101 / 107; B1 H12 1280 x 9000 53.6 /
+// 53.7).  Choices beyond the first stay within the fixed scratch array, so that
+// a call with it and one with the queried workspace take the same.
 //
 // A causal mask that hides more than 2/9 of the scores (`hides`) makes
 // items of unequal length, which even out only over several of them per unit:
@@ -131,7 +135,8 @@ SplitChoices prefill_split_choices(int64_t bh, int64_t Nq, int64_t Nk, int64_t d
     const auto fits = [&](int64_t s) { return prefill_ws_bytes(bh, Nq, d, (int)s) <= moa::kNoallocScratchBytes; };
     const int64_t wide_cap = d == 64 ? cap / 2 : cap;
     const bool one_pass = d == 64 && s1 == 1 && sw == 2;
-    if (Nq > 128 && sw <= wide_cap && sw >= 2 * s1 && sw >= s2 && sw > 1 && !one_pass && fits(sw))
+    const bool few_heads = d == 64 && bh < 8 && Nk < 16384 && s1 * items >= sw * wide_items;
+    if (Nq > 128 && sw <= wide_cap && sw >= 2 * s1 && sw >= s2 && sw > 1 && !one_pass && !few_heads && fits(sw))
         add(sw, true);
     if (200 * s1 < 85 * s2 && s2 > 1 && fits(s2)) add(s2, false);
     if (s1 > 1) add(s1, false);
