@@ -408,3 +408,16 @@ def test_prefill_queries_cover_the_causal_choice():
             s = moa.moa_attn_num_splits(1, bh, n, n, d, d, 0)
             assert s >= rounded_up >= 2
             assert moa.moa_attn_workspace_bytes(1, bh, n, n, d, d, 0) >= bh * n * s * (d + 2) * 4
+
+
+@pytest.mark.parametrize("case,want", [
+    ((16, 1572, 8115, 64), 1),      # one 128-query item per tile fills the round: no two wide splits
+    ((16, 1572, 8115, 128), 2),
+    ((4, 3800, 8600, 64), 2),       # few heads: narrow splits that fill the round as well
+    ((12, 1280, 9000, 64), 4),      # more heads: wide ones
+    ((4, 3800, 17000, 64), 4),      # more keys: wide ones
+    ((41, 18, 15038, 128), 6),      # one round of narrow splits, not seven in two
+])
+def test_prefill_split_counts_at_the_lines(case, want):
+    bh, nq, nk, d = case
+    assert moa.moa_attn_num_splits(1, bh, nq, nk, d, d) == want
