@@ -727,7 +727,12 @@ hipError_t launch_dkdv(const BwdProblem& p, int cus, hipStream_t stream) {
 //   B4 H12 2K causal, d = 64 (384 / 768)    124             128
 //   16K causal, B1 H32, d = 128             6610            6840
 //
-// A 128-query item costs about 11/20 of a 256-query one.
+// A 128-query item costs about 11/20 of a 256-query one.  Up to 128 queries a
+// head is one item either way, and the second key stream has to earn its merge
+// (B2 H15, both sides with the better dK, dV kernel):
+//   61 x 61 d = 128 14.6 / 16.2, 64 x 64 d = 64 9.6 / 10.6, 128 x 128 d = 128
+//   19.0 / 21.3; 128 x 384 d = 128 26.0 / 27.6, 64 x 512 27.0 / 27.2; 128 x 192
+//   d = 64 13.6 / 14.6, 64 x 256 13.1 / 13.1, 128 x 384 16.7 / 16.6
 //
 //   dK, dV                             128-key items    64-key items, 2 query streams
 //   B1 H8 1K, d = 128 (64 / 128)            58.5            50.0
@@ -736,6 +741,12 @@ hipError_t launch_dkdv(const BwdProblem& p, int cus, hipStream_t stream) {
 //   B2 H8 1500, d = 128 (192 / 384)         82.9            97.4
 //   B1 H20 1K, d = 64 (160 / 320)           40.2            46.7
 //   B1 H5 8K causal, d = 128 (320 / 640)    366             363
+//   B2 H15 64 x 64, d = 128 (30 / 30)       14.2            15.0
+//   same, d = 64                            9.6             9.9
+//   B2 H15 65 x 64, d = 64 (30 / 30)        11.0            11.0
+//   B2 H15 64 x 128, d = 128 (30 / 60)      18.2            16.7
+//
+// (one 64-key item per head with at most one 64-query stage has nothing to split)
 //
 //   dK, dV, d = 64                     128-key items    256-key items (NKB = 2)
 //   B2 H16 4K (1024 / 512)                  488             449
@@ -755,14 +766,16 @@ hipError_t launch(const BwdProblem& p, hipStream_t stream) {
     // D and dQ (both have nothing to do without queries)
     if (p.bh > 0 && p.nq > 0) {
         const long long i1 = (long long)p.bh * ((p.nq + 255) / 256), i2 = (long long)p.bh * ((p.nq + 127) / 128);
-        const bool split = CAUSAL ? i1 < cus : 20 * rounds(i1, cus) > 11 * rounds(i2, cus);
+        const bool short_keys = p.nq <= 128 && p.nk <= (D == 128 ? 384 : 192);
+        const bool split = !short_keys && (CAUSAL ? i1 < cus : 20 * rounds(i1, cus) > 11 * rounds(i2, cus));
         e = split ? launch_dq<D, CAUSAL, OUT_BF16, 2>(p, cus, stream)
                   : launch_dq<D, CAUSAL, OUT_BF16, 1>(p, cus, stream);
         if (e != hipSuccess) return e;
     }
     // dK, dV (zero when there are no queries)
     const long long k1 = (long long)p.bh * ((p.nk + 127) / 128);
-    if (CAUSAL ? k1 < cus : 2 * k1 <= cus) return launch_dkdv<D, CAUSAL, OUT_BF16, 1, 32, 2>(p, cus, stream);
+    const bool one_stage = p.nq <= 64 && p.nk <= 64;
+    if (!one_stage && (CAUSAL ? k1 < cus : 2 * k1 <= cus)) return launch_dkdv<D, CAUSAL, OUT_BF16, 1, 32, 2>(p, cus, stream);
     if constexpr (D == 64) {
         const long long k2 = (long long)p.bh * ((p.nk + 255) / 256);
         if (CAUSAL ? k2 >= cus : 18 * rounds(k2, cus) <= 10 * rounds(k1, cus))

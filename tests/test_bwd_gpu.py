@@ -171,8 +171,8 @@ def test_bwd_many_items_selected_heads():
         _check(tuple(g[sl] for g in got), ref, _bounds(qs, ks, vs, gs, scale, True), TOL_ISOLATED)
 
 
-# Item sizes by grid (256 compute units).  dQ: 256 heads take 256-query items, 97 rows without the
-# mask 128-query items in two key streams, as do 16 heads.  dK, dV: 256 heads of up to 257 keys take
+# Item sizes by grid (256 compute units).  dQ: 256 heads take 256-query items in one key stream, 16
+# heads 128-query items in two.  dK, dV: 256 heads of up to 257 keys take
 # 256-key items at d = 64 (with the mask, the first step of every pair even) and 128-key items at d =
 # 128 (with the mask, odd first steps), 16 heads 64-key items in two query streams.  Lengths one past
 # a tile, Nq < Nk.
@@ -209,6 +209,23 @@ def test_bwd_key_items_d64(shape, causal, grad_dtype):
         ref = oracle.attention_bwd(qs, ks, vs, gs, scale=0.125, causal=causal)
         _check(tuple(g[sl] for g in got), ref, _bounds(qs, ks, vs, gs, 0.125, causal), TOL_ISOLATED,
                bf16_store=grad_dtype == "bf16")
+
+
+# Small heads, both sides of the lines up to which dQ keeps one key stream (128 queries; 192 keys at
+# d = 64, 384 at d = 128) and dK, dV one query stream (64 queries and 64 keys).
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("shape", [(1, 3, 17, 17, 128), (2, 2, 64, 64, 64), (2, 2, 64, 64, 128), (1, 3, 65, 64, 128),
+                                   (1, 3, 64, 65, 64), (1, 2, 128, 192, 64), (1, 2, 128, 193, 64), (1, 2, 129, 192, 64),
+                                   (1, 2, 128, 384, 128), (1, 2, 128, 385, 128), (1, 2, 129, 384, 128)])
+def test_bwd_small_heads(shape, causal):
+    B, H, Nq, Nk, d = shape
+    if causal and Nq > Nk:
+        pytest.skip("causal requires Nq <= Nk")
+    q, k, v, do = _inputs(B, H, Nq, Nk, d, _seed("small", shape, causal))
+    o, lse = oracle.attention(q, k, v, scale=0.125, causal=causal, with_lse=True)
+    got = _gpu_bwd(q, k, v, do, o, lse, 0.125, causal)
+    ref = oracle.attention_bwd(q, k, v, do, scale=0.125, causal=causal)
+    _check(got, ref, _bounds(q, k, v, do, 0.125, causal), TOL_ISOLATED)
 
 
 def test_bwd_deterministic():
