@@ -664,7 +664,11 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 //            the packed one loses (111 / 114, 61 / 62); the same values in two storages take
 //            one kernel, so that their results are the same bits
 //     key-split grids (fewer 256-query items than units): 127 x 512 d 64 16.5 / 14.8, d 128
-//            26.7 / 23.9; 45 x 777 15.4 / 17.4, 22.7 / 24.0
+//            26.7 / 23.9; 45 x 777 15.4 / 17.4, 22.7 / 24.0.  With few more items than units
+//            the longest of the second round stands alone, the longer the more keys: 88 x 300
+//            d 128 packed 16.1 / 14.7, 88 x 384 16.6 / 17.8, 113 x 384 21.2 / 19.4, 66 x 450
+//            18.3 / 21.3, 85 x 450 20.9 / 21.9, 100 x 450 23.6 / 22.1; d 64 66 x 450 11.1 /
+//            12.5, 85 x 450 13.1 / 12.8
 // A mask that hides less than a quarter of the scores is treated as none
 // (80 x 700 of 2000 d 128: 69.0 / 65.7).
 //
@@ -690,7 +694,8 @@ bool use_indep(long long items256, long long items128, int nq, int nk, int bh, i
     const long long W = (items128 + cus - 1) / cus, r = (items256 + cus - 1) / cus;
     const bool big = 4LL * D * bh * nk > kCacheBytes;   // bytes of K and V
     if (CAUSAL && 2LL * nq > nk) {
-        if (items256 < cus) return nk <= 512;
+        if (items256 < cus)
+            return nk <= 320 || (nk <= 512 && (D == 128 && nk > 384 ? 2 * items128 > 3 * cus : 5 * items128 > 6 * cus));
         if (D == 64) return nk <= 8192 && (!big || 10 * W <= 18 * r);
         return nk <= 896 && (W < 2 * r || r == 1);
     }

@@ -108,11 +108,14 @@ def test_rounds_of_resident_workgroups(shape):
 
 
 # Routes on both sides of the launch rule's lines (256 compute units): K and V beyond 256 MB, few
-# queries to many keys, no gain in rounds.
+# queries to many keys, no gain in rounds, few more items than units under the mask.
 @pytest.mark.parametrize("shape", [(1, 877, 158, 1300, 64, False), (1, 766, 260, 1500, 64, False),
                                    (1, 313, 181, 870, 128, False), (1, 393, 328, 700, 128, False),
                                    (1, 738, 229, 358, 128, True), (1, 256, 200, 200, 128, True),
-                                   (1, 835, 500, 1300, 64, False)],
+                                   (1, 835, 500, 1300, 64, False), (1, 86, 300, 320, 128, True),
+                                   (1, 102, 330, 330, 64, True), (1, 103, 330, 330, 64, True),
+                                   (1, 96, 400, 400, 128, True), (1, 97, 400, 400, 128, True),
+                                   (1, 70, 500, 512, 64, True)],
                          ids=lambda s: "x".join(str(int(x)) for x in s))
 def test_lines_of_the_launch_rule(shape):
     B, H, Nq, Nk, d, causal = shape
