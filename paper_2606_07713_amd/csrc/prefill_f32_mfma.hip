@@ -111,7 +111,10 @@ __global__ __launch_bounds__(W * 64, 2) void prefill_f32_mfma_kernel(
         for (int j = 0; j < CH; ++j) kf[j] = __builtin_bit_cast(float4, buffer_load16(rk, o + (uint32_t)j * 64u));
     };
     // V rows of block `kt`: the four keys 4h .. 4h + 3 that this lane's score
-    // registers hold, the NB values from column NB * m.
+    // registers hold, the NB values from column NB * m.  Rows past Nk read as
+    // zero (the last row in their place would turn an infinity in it, times the
+    // weight 0 of a key that does not exist, into NaN).
+    constexpr uint32_t kPastEnd = 0x80000000u;   // past any head slice (< 2 GiB)
     float4 vf[4][NB / 4];
     auto load_v = [&](int kt) {
         const uint32_t col = (uint32_t)m * (NB * 4u);
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(W * 64, 2) void prefill_f32_mfma_kernel(
         const uint32_t o = (uint32_t)row * vrb + col;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint32_t oi = whole ? o + (uint32_t)i * vrb : (uint32_t)min(row + i, Nk - 1) * vrb + col;
+            const uint32_t oi = whole || row + i < Nk ? o + (uint32_t)i * vrb : kPastEnd;
 #pragma unroll
             for (int j = 0; j < NB / 4; ++j)
                 vf[i][j] = __builtin_bit_cast(float4, buffer_load16(rv, oi + j * 16u));

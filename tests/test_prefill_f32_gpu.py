@@ -37,6 +37,21 @@ def test_f32_matrix_core_prefill(shape):
     assert max_err(lse, ref_lse) <= 1e-5 * max(1.0, np.abs(ref_lse).max())
 
 
+# Lengths that end inside a 16-key block (in every lane group of it), four and eight key streams.
+@pytest.mark.parametrize("shape", [(1, 16, 300, 300, 64), (1, 4, 1000, 1000, 64), (1, 6, 1000, 995, 128), (2, 32, 70, 33, 128)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_f32_infinity_in_the_last_value(shape, value):
+    # Keys past Nk have no weight: an infinite element of the last V row reaches its own column of
+    # every row that sees the key, as itself, and nothing else.
+    B, H, Nq, Nk, d = shape
+    q, k, v = gen(B, H, Nq, Nk, d, "f32", seed=sum(shape))
+    v[:, :, -1, 3] = value
+    o = run_gpu(q, k, v)
+    assert (o[..., 3] == value).all()
+    assert np.isfinite(np.delete(o, 3, axis=-1)).all()
+
+
 # d = 128, 65 to 128 tiles of 16 rows: 8 lanes per row up to 224 keys, the matrix cores beyond.
 @pytest.mark.parametrize("shape", [(1, 5, 211, 211), (2, 4, 200, 224), (1, 8, 250, 225), (3, 4, 97, 160)],
                          ids=lambda s: "x".join(map(str, s)))
