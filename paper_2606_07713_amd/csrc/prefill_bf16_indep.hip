@@ -22,6 +22,12 @@
 // spilled in the loop) were slower on every grid: 176 x 777 45.0 against 43.5
 // us, 102 x 1500 causal 50.4 / 45.2, packed B4 H12 3000 causal 95.3 / 71.8.  At d =
 // 128 three waves spilled heavily (four times slower).
+//
+// The softmax step, the tile layout and the schedule are shared with
+// prefill_bf16.hip; the operand addresses and the output rows are written out in
+// both.  As common functions they left these kernels as they are and made the
+// prologue of the key split with strided rows 0.3 to 0.5 us longer (packed d =
+// 128, B4 H24 63 x 212 10.1 -> 10.5 us, B4 H5 359 x 359 causal 12.8 -> 13.3).
 #include <algorithm>
 #include <type_traits>
 
