@@ -733,6 +733,14 @@ hipError_t launch_dkdv(const BwdProblem& p, int cus, hipStream_t stream) {
 //   61 x 61 d = 128 14.6 / 16.2, 64 x 64 d = 64 9.6 / 10.6, 128 x 128 d = 128
 //   19.0 / 21.3; 128 x 384 d = 128 26.0 / 27.6, 64 x 512 27.0 / 27.2; 128 x 192
 //   d = 64 13.6 / 14.6, 64 x 256 13.1 / 13.1, 128 x 384 16.7 / 16.6
+// Nor does a 128-query item cost so little with few keys, where prologue and
+// merge weigh more: if the items then need more rounds, 256-query ones stay up
+// to 512 keys (whole calls):
+//   causal, one round against two: 130 x 139 d = 64 18.7 / 24.8, d = 128 29.3 /
+//   41.2, 130 x 256 d = 128 44.9 / 52.2, 100 x 400 51.4 / 60.3; 53 x 520 53.1 /
+//   52.1, 40 x 1000 78.9 / 69.3
+//   no mask, d = 128: 190 x 300 of 89 keys [2, 3 rounds] 41.6 / 51.2, of 512 109 / 121;
+//   233 x 520 of 89 [3, 5] 70.4 / 83.0; 130 x 520 [2, 3] of 900 118 / 116
 //
 //   dK, dV                             128-key items    64-key items, 2 query streams
 //   B1 H8 1K, d = 128 (64 / 128)            58.5            50.0
@@ -766,7 +774,8 @@ hipError_t launch(const BwdProblem& p, hipStream_t stream) {
     // D and dQ (both have nothing to do without queries)
     if (p.bh > 0 && p.nq > 0) {
         const long long i1 = (long long)p.bh * ((p.nq + 255) / 256), i2 = (long long)p.bh * ((p.nq + 127) / 128);
-        const bool short_keys = p.nq <= 128 && p.nk <= (D == 128 ? 384 : 192);
+        const bool short_keys = (p.nq <= 128 && p.nk <= (D == 128 ? 384 : 192)) ||
+                                (rounds(i2, cus) > rounds(i1, cus) && p.nk <= 512);
         const bool split = !short_keys && (CAUSAL ? i1 < cus : 20 * rounds(i1, cus) > 11 * rounds(i2, cus));
         e = split ? launch_dq<D, CAUSAL, OUT_BF16, 2>(p, cus, stream)
                   : launch_dq<D, CAUSAL, OUT_BF16, 1>(p, cus, stream);

@@ -172,10 +172,9 @@ def test_bwd_many_items_selected_heads():
 
 
 # Item sizes by grid (256 compute units).  dQ: 256 heads take 256-query items in one key stream, 16
-# heads 128-query items in two.  dK, dV: 256 heads of up to 257 keys take
-# 256-key items at d = 64 (with the mask, the first step of every pair even) and 128-key items at d =
-# 128 (with the mask, odd first steps), 16 heads 64-key items in two query streams.  Lengths one past
-# a tile, Nq < Nk.
+# heads 128-query items in two.  dK, dV: 256 heads of 129 or 130 keys take 256-key items at d = 64
+# without the mask, the others of 256 heads 128-key items (161 keys with the mask: odd first steps),
+# 16 heads 64-key items in two query streams.  Lengths one past a tile, Nq < Nk.
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("shape,scale", [((8, 32, 129, 129, 64), 0.125), ((8, 32, 97, 130, 64), -0.2),
                                          ((8, 32, 130, 257, 64), 0.125), ((8, 32, 129, 161, 128), 0.09),
@@ -193,11 +192,11 @@ def test_bwd_item_sizes(shape, scale, causal):
 
 
 # 32 heads of 1000, d = 64: dQ in 128-query items, dK, dV in 128-key items of one query stream (with
-# the mask, odd first steps).  256 heads, 161 keys: 256-key items whose first step is odd under the
-# mask (query 32 is the first to see key 64).
+# the mask, odd first steps).  256 heads of 161 keys: 256-key items without the mask; 110 heads of 577
+# keys under it, their first steps odd (query 32 is the first to see key 64).
 @pytest.mark.parametrize("grad_dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("shape", [(4, 8, 1000, 1000, 64), (8, 32, 129, 161, 64)])
+@pytest.mark.parametrize("shape", [(4, 8, 1000, 1000, 64), (8, 32, 129, 161, 64), (2, 55, 545, 577, 64)])
 def test_bwd_key_items_d64(shape, causal, grad_dtype):
     B, H, Nq, Nk, d = shape
     q, k, v, do = _inputs(B, H, Nq, Nk, d, _seed("key items", shape, causal))
@@ -226,6 +225,24 @@ def test_bwd_small_heads(shape, causal):
     got = _gpu_bwd(q, k, v, do, o, lse, 0.125, causal)
     ref = oracle.attention_bwd(q, k, v, do, scale=0.125, causal=causal)
     _check(got, ref, _bounds(q, k, v, do, 0.125, causal), TOL_ISOLATED)
+
+
+# Many small heads, where the items of dQ in two key streams (130 to 190 heads) or the 256-key items
+# of dK, dV (300 heads under the mask) would fill more rounds or stand half empty, and lengths past
+# those lines (dQ 520 and 530 keys, dK, dV 640), which take them.
+@pytest.mark.parametrize("shape,causal", [((130, 139, 139, 64), True), ((130, 139, 139, 128), True), ((190, 257, 89, 128), False),
+                                          ((130, 257, 520, 64), False), ((45, 513, 530, 128), True), ((300, 44, 44, 64), True),
+                                          ((150, 130, 640, 64), True)], ids=str)
+def test_bwd_many_small_heads(shape, causal):
+    H, Nq, Nk, d = shape
+    q, k, v, do = _inputs(1, H, Nq, Nk, d, _seed("many small", shape, causal))
+    o, lse = oracle.attention(q, k, v, scale=0.125, causal=causal, with_lse=True)
+    got = _gpu_bwd(q, k, v, do, o, lse, 0.125, causal)
+    for h in (0, H // 2, H - 1):
+        sl = (slice(0, 1), slice(h, h + 1))
+        qs, ks, vs, gs = (x[sl] for x in (q, k, v, do))
+        ref = oracle.attention_bwd(qs, ks, vs, gs, scale=0.125, causal=causal)
+        _check(tuple(x[sl] for x in got), ref, _bounds(qs, ks, vs, gs, 0.125, causal), TOL_ISOLATED)
 
 
 def test_bwd_deterministic():
