@@ -762,8 +762,15 @@ hipError_t launch_dkdv(const BwdProblem& p, int cus, hipStream_t stream) {
 //   B4 H12 2K causal (768 / 384)            124             119
 //   B4 H16 700 causal (384 / 192)           42.9            51.0
 //   B4 H8 1000 (256 / 128)                  49.7            59.7
+//   300 x 44 causal (300 / 300)             18.0            20.4
+//   600 x 256 causal (1200 / 600)           80.8            89.4
+//   400 x 512 causal (1600 / 800)           134             144
+//   400 x 700 causal (2400 / 1200)          213             205
+//   32 x 2048 causal (512 / 256)            97.6            112
+//   50 x 2048 causal (800 / 400)            133             125
 //
-// A 256-key item costs about 18/10 of a 128-key one.
+// A 256-key item costs about 18/10 of a 128-key one; under the mask it needs
+// more than 512 keys, and more items than units, to be evened out.
 long long rounds(long long items, int cus) { return (items + cus - 1) / cus; }
 
 template <int D, bool CAUSAL, bool OUT_BF16>
@@ -787,7 +794,7 @@ hipError_t launch(const BwdProblem& p, hipStream_t stream) {
     if (!one_stage && (CAUSAL ? k1 < cus : 2 * k1 <= cus)) return launch_dkdv<D, CAUSAL, OUT_BF16, 1, 32, 2>(p, cus, stream);
     if constexpr (D == 64) {
         const long long k2 = (long long)p.bh * ((p.nk + 255) / 256);
-        if (CAUSAL ? k2 >= cus : 18 * rounds(k2, cus) <= 10 * rounds(k1, cus))
+        if (CAUSAL ? 4 * k2 >= 5 * cus && p.nk > 512 : 18 * rounds(k2, cus) <= 10 * rounds(k1, cus))
             return launch_dkdv<D, CAUSAL, OUT_BF16, 2, 64, 1>(p, cus, stream);
     }
     return launch_dkdv<D, CAUSAL, OUT_BF16, 1, 64, 1>(p, cus, stream);
