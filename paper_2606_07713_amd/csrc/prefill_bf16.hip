@@ -649,6 +649,8 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 //   item each (the key split would need two rounds):
 //     120 x 300 d 64 14.8 / 12.3, d 128 22.2 / 19.4; 40 x 1100 30.2 / 29.4, 45.3 / 43.4;
 //     45 x 1100 29.7 / 30.5, 50.0 / 46.7
+//     one key tile, d 128 packed: 125 x 500 of 61 11.8 / 13.2, 250 x 200 of 64 10.9 / 11.6
+//     (of 65: 18.1 / 16.0); d 64 8.4 / 8.3
 //   unmasked, more: W, r
 //     d 64:  69 x 777 [2, 2] 37.8 / 21.8; 96 x 777 [3, 2] 37.5 / 28.2; 73 x 1500 [4, 2]
 //            61.1 / 65.2; 102 x 1500 [5, 3] 94.1 / 78.8; 119 x 1500 [6, 3] 95.8 / 96.4
@@ -702,7 +704,7 @@ bool use_indep(long long items256, long long items128, int nq, int nk, int bh, i
         if (D == 64) return nk <= 8192 && (!big || 10 * W <= 18 * r);
         return nk <= 896 && (W < 2 * r || r == 1);
     }
-    if (items256 < cus) return D == 128 || nk < 1024 || 2 * items128 <= 3 * cus;
+    if (items256 < cus) return D == 128 ? nk > BN : nk < 1024 || 2 * items128 <= 3 * cus;
     if (D == 64) return big ? 10 * W <= 17 * r : 13 * W < 25 * r;
     if ((big && 2 * W > 3 * r) || ((nk >= 2LL * nq || (r == 2 && nk > 640)) && 2 * W >= 3 * r)) return false;
     return 3 * W < 5 * r && !use_key_split<CAUSAL>(items256, items128, nk, cus);
