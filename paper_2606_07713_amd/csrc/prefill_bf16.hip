@@ -691,6 +691,11 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 //   d 128, causal, no gain in rounds: 888 x 469 of 833 [14, 7] 230 / 273, 738 x 229 of 358
 //                    [6, 3] 61 / 65, 452 x 480 of 873 [8, 4] 120 / 132; one round alone gains
 //                    (packed: 128 x 400 [2, 1] 22.4 / 20.6, 256 x 256 [2, 1] 19.0 / 18.4)
+//   d 128, causal, a last round nearly empty and no shorter tail (contiguous and packed):
+//                    93 x 707 [3, 2] 30.0 / 35.2, 90 x 768 [3, 2] 29.8 / 35.6 and 30.6 / 39.0, 150 x
+//                    512 [3, 2] 29.8 / 30.5 and 30.5 / 32.5, 177 x 768 [5, 3] 56.9 / 58.7 and 58.3 /
+//                    61.7; 110 x 640 (five tiles of 128 for three of 256) [3, 2] 35.1 / 32.9 and
+//                    36.2 / 35.6, 150 x 400 [3, 2] 28.6 / 27.1 and 29.8 / 28.6
 constexpr long long kCacheBytes = 256LL << 20;
 
 template <int D, bool CAUSAL>
@@ -702,6 +707,8 @@ bool use_indep(long long items256, long long items128, int nq, int nk, int bh, i
         if (items256 < cus)
             return nk <= 320 || (nk <= 512 && (D == 128 && nk > 384 ? 2 * items128 > 3 * cus : 5 * items128 > 6 * cus));
         if (D == 64) return nk <= 8192 && (!big || 10 * W <= 18 * r);
+        if (nk > 448 && r == 2 && W == 3 && 3 * items128 > 5 * items256) return false;
+        if (nk > 640 && r <= 5 && 5 * items128 > 9 * items256) return false;
         return nk <= 896 && (W < 2 * r || r == 1);
     }
     if (items256 < cus) return D == 128 ? nk > BN : nk < 1024 || 2 * items128 <= 3 * cus;

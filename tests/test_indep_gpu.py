@@ -116,7 +116,9 @@ def test_rounds_of_resident_workgroups(shape):
                                    (1, 102, 330, 330, 64, True), (1, 103, 330, 330, 64, True),
                                    (1, 96, 400, 400, 128, True), (1, 97, 400, 400, 128, True),
                                    (1, 70, 500, 512, 64, True), (1, 80, 700, 700, 128, False),
-                                   (1, 125, 500, 61, 128, False), (1, 125, 500, 65, 128, False)],
+                                   (1, 125, 500, 61, 128, False), (1, 125, 500, 65, 128, False),
+                                   (1, 93, 707, 707, 128, True), (1, 110, 580, 580, 128, True),
+                                   (1, 177, 700, 700, 128, True)],
                          ids=lambda s: "x".join(str(int(x)) for x in s))
 def test_lines_of_the_launch_rule(shape):
     B, H, Nq, Nk, d, causal = shape
