@@ -686,7 +686,8 @@ bool use_key_split(long long items_pp, long long items_ks, int nk, int cus) {
 //   d 128, few queries to many keys: 313 x 181 of 870 [3, 2] 57 / 61, 186 x 297 of 589 [3, 2]
 //                    44 / 46, 360 x 157 of 441 [3, 2] 35 / 33; 393 x 328 of 897 [5, 4] 122 / 100
 //   d 128, three rounds against two, contiguous and packed: 87 x 800 55.7 / 56.5 and 58.2 / 60.4, 87
-//                    x 1000 67.1 / 68.5 and 70.9 / 73.6, 71 x 1003 packed 68.7 / 72.0; 116 x 600
+//                    x 1000 67.1 / 68.5 and 70.9 / 73.6, 71 x 1003 packed 68.7 / 72.0, 185 x 512
+//                    41.7 / 41.6 and 43.0 / 45.7, 129 x 512 packed 42.3 / 43.9; 116 x 600
 //                    44.6 / 42.7 and 46.5 / 46.9, 290 x 200 26.9 / 24.7 and 28.1 / 27.4
 //   d 128, causal, no gain in rounds: 888 x 469 of 833 [14, 7] 230 / 273, 738 x 229 of 358
 //                    [6, 3] 61 / 65, 452 x 480 of 873 [8, 4] 120 / 132; one round alone gains
@@ -713,7 +714,9 @@ bool use_indep(long long items256, long long items128, int nq, int nk, int bh, i
     }
     if (items256 < cus) return D == 128 ? nk > BN : nk < 1024 || 2 * items128 <= 3 * cus;
     if (D == 64) return big ? 10 * W <= 17 * r : 13 * W < 25 * r;
-    if ((big && 2 * W > 3 * r) || ((nk >= 2LL * nq || (r == 2 && nk > 640)) && 2 * W >= 3 * r)) return false;
+    // three rounds against two: no shorter tail, or many keys
+    const bool even = r == 2 && (nk > 640 || (nk > 384 && 5 * items128 > 9 * items256));
+    if ((big && 2 * W > 3 * r) || ((even || nk >= 2LL * nq) && 2 * W >= 3 * r)) return false;
     return 3 * W < 5 * r && !use_key_split<CAUSAL>(items256, items128, nk, cus);
 }
 

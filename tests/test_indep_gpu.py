@@ -1,6 +1,6 @@
 """The independent-workgroup bf16 prefill (grids of uneven rounds) against the fp64 oracle on
-sampled rows; the launch rule sends every shape here to it on a 256-unit GPU.  Tolerances as
-everywhere: 2e-2 for O, 4e-3 (bf16 weights) plus fp32 rounding for LSE."""
+sampled rows; the launch rule sends the shapes here to it on a 256-unit GPU, except where a test
+names another layout or both sides of a line.  Tolerances as everywhere: 2e-2 for O, 4e-3 (bf16 weights) plus fp32 rounding for LSE."""
 import zlib
 
 import numpy as np
@@ -66,7 +66,9 @@ def test_independent_workgroups_packed_layout(d, causal):
 
 
 def test_more_items_than_resident_workgroups():
-    # Several items per workgroup, the last layer of items partly empty.
+    # Several items per workgroup, the last layer of items partly empty; twice as many 128-query
+    # rounds as 256-query ones, so the ping-pong layout (test_rounds_of_resident_workgroups has the
+    # independent workgroups).
     q, k, v = gen(1, 700, 200, 190, 64, "bf16", seed=77)
     o, lse = run_gpu(q, k, v, out_dtype="f32", return_lse=True)
     _check(q, k, v, o, lse, False)
